@@ -12,21 +12,36 @@
 // the scalar recurrence of the coefficients over the 16 tokens of a chunk (a
 // <= 15-term right-looking update plus the E-step, per token) is sequential.
 // This is the algebra of the delta-rule chunk form that App. D builds on,
-// applied to the exact nonlinear recurrence one chunk at a time.  The
-// schedule puts only a 16 x 16 product between the recurrence of one chunk
-// and that of the next.  With C_n the coefficients of chunk n:
-//   P_{n+1} = K_{n+1} S_{n+1} = K_{n+1} S_n + (K_{n+1} K_n^T) C_n.
-// While the sequential wave runs the recurrence of chunk n (phase B), the
-// matrix-core waves do everything that does not need C_n:
+// applied to the exact nonlinear recurrence one chunk at a time.  With C_n the
+// coefficients of chunk n,
+//   P_{n+1} = K_{n+1} S_{n+1} = K_{n+1} S_n + (K_{n+1} K_n^T) C_n,
+// and with G'_n = K_{n+1} K_n^T the second term is formed while the sequential
+// wave runs chunk n: the matrix-core waves take the coefficients of its first 12
+// tokens, published at a block barrier in the middle of the chunk, and the
+// sequential wave the last four.  Its own updates - of the later tokens of the
+// chunk (G_n = K_n K_n^T), and those - are fp32 products of 4x4x1 blocks
+// (v_mfma_f32_4x4x1_16b_f32: lane = column, four tokens per instruction, all 16
+// blocks taking the same four Gram values).  So the next chunk's predictions are
+// ready at the chunk's second barrier.  During chunk n the other waves form
 //   S_n = S_{n-1} + K_{n-1}^T C_{n-1}          (state update of the previous chunk)
 //   Y_{n-1} += tril(A_{n-1}) C_{n-1}; pi^q Y    (retrieval of the previous chunk)
 //   o_{n-2} = sum_j pi^q Y                      (output of the chunk before)
-//   Y0_n = Q_n S_n,  X_{n+1} = K_{n+1} S_n,  G'_n = K_{n+1} K_n^T (each wave,
-//   in registers),  G_{n+1} = K_{n+1} K_{n+1}^T,  pi^q_n, beta_{n+1}, ...
-//   and the HBM -> LDS transfer of chunk n+2 (direct global-to-LDS loads).
-// After C_n is published they form P_{n+1} = X_{n+1} + G'_n C_n (three
-// 16 x 16 x 16 products) and the next recurrence starts.  Two block barriers
-// per chunk.
+//   Y0_n = Q_n S_n,  K_{n+1} S_n,  G_{n+1}, G'_{n+1}, A_{n+1} = Q_{n+1} K_{n+1}^T
+//   (once per block),  pi^q_n,  beta_{n+2}, ..., from the middle of the chunk on B_{n+1} =
+//   K_{n+1} S_n + G'_n C_n (tokens 0 .. 11 of C_n), and the HBM -> LDS transfers of K, beta and key-prior
+//   logits and v of chunk n+3 and of Q and the query-prior logits of chunk n+2
+//   (direct global-to-LDS loads).
+//
+// Bound: the sequential wave's instruction count, and where a block has 64
+// columns (four tile waves on the same four SIMDs) the issue slots of all waves.
+// One launch, before (the P-step of all 16 tokens between two barriers, the
+// updates as scalar-times-vector FMAs with the Gram rows read per token) and now:
+//   B=4 H=8  T=2048  D=64  J=4          0.157 -> 0.141 ms
+//   B=8 H=16 T=4096  D=128 J=4          1.634 -> 1.393 ms
+//   B=2 H=8  T=16384 D=128 J=8          1.637 -> 1.450 ms
+//   temporal, B=4 H=8 T=2043 D=64 J=4   0.183 -> 0.171 ms
+// Giving the sequential wave all 16 tokens of the cross term (64 products more a
+// chunk, no second barrier) was slower: 0.181 and 1.83 ms on the first two.
 //
 // Precision.  bf16 q and k enter the matrix cores unrounded.  fp32 operands
 // (the state, the coefficients, the Gram products) are split into a bf16 high
@@ -38,8 +53,7 @@
 // w holding the Dk x 16 state tile of columns 16w..16w+15 in MFMA accumulator
 // layout; wave NW is the sequential wave.  Raw chunk inputs sit in LDS rings
 // of a few chunk slots each; K and Q rows are stored with their 16-byte pieces permuted
-// by row (piece p of row t at slot p ^ (t mod pieces)) so that the 16 lanes
-// reading one column range hit distinct banks.
+// by row (kperm) so that the 16 lanes reading one column range hit distinct banks.
 //
 // Newton mode (App. D).  The same kernel evaluates the chunkwise quasi-Newton
 // iteration of App. D.1-D.3.  Sweep i linearises the recurrence around the
@@ -74,11 +88,12 @@ typedef short short4v __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kC = 16;    // tokens per chunk
-// LDS ring slots per input, by how long a chunk stays in use after it lands
-// (it lands two chunks ahead of the sequential wave):
-constexpr int kRingKQ = 4;  // K, Q: chunks n-1 .. n+2 (state update, retrieval of n-1)
-constexpr int kRingQP = 3;  // query-prior logits, Newton predictions: n .. n+2
-constexpr int kRingS = 2;   // beta and key-prior logits, v: n+1, n+2 (staged one chunk ahead)
+// LDS ring slots per input, by how long a chunk stays in use after it lands (n:
+// the chunk that the sequential wave runs):
+constexpr int kRingK = 5;   // K: chunks n-1 (state update) .. n+2 (Gram products), n+3 lands
+constexpr int kRingQ = 3;   // Q: n, n+1 (Gram product), n+2 lands
+constexpr int kRingQP = 3;  // query-prior logits: n, n+2 lands; Newton predictions: n+1 .. n+3
+constexpr int kRingS = 2;   // beta and key-prior logits, v: n+2 (staged), n+3 lands
 constexpr int kTP = kC + 4;  // row of a column-major [column][token] staging array
 constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
@@ -91,6 +106,25 @@ constexpr float kInvS = 1.17741002251547469101f;   // 1 / kS
 
 __device__ __forceinline__ floatx4 mfma32(bf16x8 a, bf16x8 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// acc[i] += A[i] c for this lane's column, A the four values that lanes 4 S ..
+// 4 S + 3 of g hold (the A operand of block S, taken by all 16 blocks)
+template <int S>
+__device__ __forceinline__ floatx4 mfma4(float g, float c, floatx4 acc) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(g, c, acc, 4, S, 0);
+}
+// The U-th deferred update of the coefficient c of token S (scan_pipe_kernel): OWN
+// groups of the chunk's own tokens (the last OWN of D, A operands g), then the
+// groups of the next chunk's tokens (X, block 4 (S - kEarly) + group of gx).
+constexpr int kEarly = kC - 4;   // the first token that the tile waves' P-step leaves out
+template <int S, int U, int OWN>
+__device__ __forceinline__ void defer1(float c, floatx4 (&D)[kC / 4], floatx4 (&X)[kC / 4],
+                                       const float (&g)[kC / 4], float gx) {
+    if constexpr (U < OWN) {
+        D[kC / 4 - OWN + U] = mfma4<S>(g[kC / 4 - OWN + U], c, D[kC / 4 - OWN + U]);
+    } else if constexpr (S >= kEarly && U - OWN < kC / 4) {
+        X[U - OWN] = mfma4<4 * (S - kEarly) + U - OWN>(gx, c, X[U - OWN]);
+    }
 }
 __device__ __forceinline__ floatx4 mfma16(short4v a, short4v b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -118,10 +152,6 @@ __device__ __forceinline__ void split4v(float x0, float x1, float x2, float x3, 
 // compiler's own wait insertion knows the transfers have landed and does not
 // add waits of its own before later LDS reads (such a wait would also wait for
 // every global store in flight).
-template <bool B>
-struct BoolTag {
-    static constexpr bool value = B;
-};
 template <int V>
 struct IntTag {
     static constexpr int value = V;
@@ -193,8 +223,8 @@ template <int DK, int J, int DB, int MD>
 struct PSmem {
     static constexpr bool NT = MD == 1, TP = MD == 2;
     using C = PCfg<DK, J, DB>;
-    uint4 k[kRingKQ][C::KPIECES];
-    uint4 q[kRingKQ][C::KPIECES];
+    uint4 k[kRingK][C::KPIECES];
+    uint4 q[kRingQ][C::KPIECES];
     uint4 lb[kRingS][C::LPIECES];
     uint4 lk[kRingS][C::LPIECES];
     uint4 lq[kRingQP][C::LPIECES];
@@ -216,8 +246,14 @@ struct PSmem {
     alignas(16) float gs[TP ? 2 : 1][TP ? DB : 1][kC + 4];   // temporal: 1 - g^k, [dim][token]
     float gqs[TP ? 3 : 1][kC][TP ? DB : 1];                  // temporal: g^q, [token][dim]
     float pq[TP ? 3 : 2][kC][C::NP];    // query prior (temporal: the running prior, 3 slots)
-    alignas(16) float g[2][kC][kC + 4];    // K_n K_n^T, for the sequential wave
-    // chunk-start predictions and coefficients, [C::prow(column)][token]
+    // for the sequential wave, as A operands of its 4x4 products: -K_n K_n^T and
+    // -K_{n+1} K_n^T, [token group m][4 s + i] = the value of tokens 4 m + i and
+    // s; and -k_{t+1} . k_t
+    alignas(16) float g[2][kC * kC], gx[2][64], gsub[2][kC];
+    // for the tile waves, as A operands: G'_n and tril(Q_n K_n^T) (slot n mod 3),
+    // the bf16 high parts and residuals of a lane's four values
+    uint4 ga[2][64], qa[3][64];
+    // B_n and the coefficients, [C::prow(column)][token]
     // (C::prow(N): the idle lanes' row of c)
     float p[2][C::NRP][kTP];
     float c[2][C::NRP + 1][kTP];
@@ -227,41 +263,54 @@ struct PSmem {
     int near;                  // Newton: its change was within 4 tol (the next may be the last)
 };
 
+// Key indices of the state tile's accumulator rows: row 4 lg + r of step it is
+// key krow(it, lg) + r.  Steps 2 s and 2 s + 1 share 32 key indices so that a
+// lane's eight rows are consecutive, and with them the eight values (16 bytes)
+// of a K or Q row that a 32-deep product takes.
+template <int DK>
+__device__ __forceinline__ constexpr int krow(int it, int lg) {
+    return DK == 16 ? 4 * lg : 32 * (it / 2) + 8 * lg + 4 * (it & 1);
+}
+// K and Q tiles in LDS: 16-byte piece p of row t sits at slot t KPC + (p ^
+// kperm(t)).  The 16 rows of one piece then fall in distinct 16-byte groups of
+// the 256-byte bank row (16-byte fragment reads), and the eight rows by four
+// pieces of a transposing read on each group twice at most.
+template <int DK>
+__device__ __forceinline__ constexpr int kperm(int t) {
+    constexpr int KPC = DK / 8;
+    return KPC == 16 ? ((t & 3) << 2) | (t >> 2)
+           : KPC == 8 ? ((t & 2) << 1) | ((t >> 2) & 1) | ((t >> 2) & 2)
+           : KPC == 4 ? (t >> 2) & 3
+                      : (t >> 3) & 1;
+}
+// the 16-byte piece p of row t of a tile
+template <int DK>
+__device__ __forceinline__ uint4 tile8(const uint4 *tile, int t, int p) {
+    return tile[t * (DK / 8) + (p ^ kperm<DK>(t))];
+}
 // Four consecutive bf16 (as raw bits) of row t from element i (i % 4 == 0)
 // of a row-permuted K or Q tile.
 template <int DK>
 __device__ __forceinline__ uint2 tile4(const uint4 *tile, int t, int i) {
-    constexpr int KPC = DK / 8;
-    const int slot = t * KPC + ((i >> 3) ^ (t & (KPC - 1)));
+    const int slot = t * (DK / 8) + ((i >> 3) ^ kperm<DK>(t));
     return reinterpret_cast<const uint2 *>(tile + slot)[(i >> 2) & 1];
 }
 
 // Transposed 16 x 16 block of a row-permuted K tile, as the A operand of a
-// 16x16x16 matrix-core step: lane (tl, lg) receives K[4 lg + mm][16 it + tl],
-// mm = 0..3, from one transposing LDS load.  In each group of 16 lanes the
-// load hands lane i element mm of the 8 bytes addressed by lane 4 mm + i / 4
-// (element i mod 4), so lane (tl, lg) addresses row 4 lg + tl / 4, key
-// indices 16 it + 4 (tl mod 4) .. + 3.
+// 16x16x16 matrix-core step: lane (tl, lg) receives K[4 lg + mm][key of row tl of
+// step it], mm = 0..3, from one transposing LDS load.  In each group of 16 lanes
+// the load hands lane i element mm of the 8 bytes addressed by lane 4 mm + i / 4
+// (element i mod 4), so lane (tl, lg) addresses row 4 lg + tl / 4, key indices
+// krow(it, tl mod 4) .. + 3.
 typedef short short4vs __attribute__((__vector_size__(8)));
 template <int DK>
 __device__ __forceinline__ short4v tile_tr(const uint4 *tile, int it, int tl, int lg) {
-    constexpr int KPC = DK / 8;
-    const int t = 4 * lg + (tl >> 2), q = tl & 3;
-    const int slot = t * KPC + ((2 * it + (q >> 1)) ^ (t & (KPC - 1)));
-    const char *p = reinterpret_cast<const char *>(tile + slot) + 8 * (q & 1);
+    const int t = 4 * lg + (tl >> 2), i = krow<DK>(it, tl & 3);
+    const int slot = t * (DK / 8) + ((i >> 3) ^ kperm<DK>(t));
+    const char *p = reinterpret_cast<const char *>(tile + slot) + 2 * (i & 4);
     const short4vs v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
         (__attribute__((address_space(3))) short4vs *)(p));
     return __builtin_bit_cast(short4v, v);
-}
-
-// A-operand fragment of rows 0..15 of a K or Q tile for the matrix-core step
-// covering key indices [32 s, 32 s + 32) (slot 8 g + m <-> key 32 s + 4 g + m,
-// and 32 s + 16 + 4 g + m - 4), or all 16 for Dk = 16.
-template <int DK>
-__device__ __forceinline__ uint4 frag32(const uint4 *tile, int tl, int lg, int s) {
-    const uint2 x0 = tile4<DK>(tile, tl, 32 * s + 4 * lg);
-    const uint2 x1 = tile4<DK>(tile, tl, 32 * s + 16 + 4 * lg);
-    return make_uint4(x0.x, x0.y, x1.x, x1.y);
 }
 
 // One wave-wide HBM -> LDS transfer: lane L moves 16 bytes from src to
@@ -296,7 +345,9 @@ __device__ __forceinline__ int first_for(int base, int mw, int nw) {
 // Tokens past T re-read token T - 1 (in range); the recurrence gives them
 // beta = 0.  In Newton mode the chunk's predictions from the previous sweep
 // ([kC][N] fp32 at pred + t0 N, the block's workspace) come along.
-template <int DK, int J, int DB, int MD, int NIW>
+// QS selects the tensors: false K, the beta and key-prior logits, v (the key
+// gates, the predictions); true Q, the query-prior logits (the query gates).
+template <int DK, int J, int DB, int MD, int NIW, bool QS>
 __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB, MD> &sm,
                                             uint32_t lds_base, int m, int t0, int b, int h,
                                             int d0, int mw, int lane, const float *pred) {
@@ -306,7 +357,7 @@ __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB,
         return lds_base + (uint32_t)(reinterpret_cast<const char *>(dst) -
                                      reinterpret_cast<const char *>(&sm));
     };
-    const int skq = m % kRingKQ, sqp = m % kRingQP, ss = m % kRingS;
+    const int sk = m % kRingK, sq = m % kRingQ, sqp = m % kRingQP, ss = m % kRingS;
     using C = PCfg<DK, J, DB>;
     const int T = a.T, H = a.H, Dv = a.Dv;
     constexpr int nk = (C::KPIECES + 63) / 64, nl = (C::LPIECES + 63) / 64;
@@ -315,13 +366,13 @@ __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB,
         // Whole chunk in range: a scalar base per tensor (row t0 of this head)
         // plus a 32-bit per-lane byte offset.
         const size_t row0 = ((size_t)b * T + t0) * H + h;
-        // K and Q rows: piece p of row t goes to slot p ^ (t mod pieces)
+        // K and Q rows: slot p of row t takes piece p ^ kperm(t)
         auto kq = [&](const void *base, uint4 *tile, int ibase) {
             const char *src = static_cast<const char *>(base) + row0 * DK * 2;
             for (int ins = first_for(ibase, mw, NIW); ins < ibase + nk; ins += NIW) {
                 const int part = ins - ibase, s = part * 64 + lane;
                 if (s < C::KPIECES) {
-                    const int t = s / C::KPC, p = s % C::KPC, gp = p ^ (t & (C::KPC - 1));
+                    const int t = s / C::KPC, p = s % C::KPC, gp = p ^ kperm<DK>(t);
                     dma16(src + (uint32_t)(t * H * DK * 2 + 16 * gp), at(tile + part * 64));
                 }
             }
@@ -338,11 +389,14 @@ __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB,
                 }
             }
         };
-        kq(a.k, sm.k[skq], 0);
-        kq(a.q, sm.q[skq], nk);
-        logit(a.lb, sm.lb[ss], 2 * nk);
-        logit(a.lk, sm.lk[ss], 2 * nk + nl);
-        logit(a.lq, sm.lq[sqp], 2 * nk + 2 * nl);
+        if constexpr (QS) {
+            kq(a.q, sm.q[sq], 0);
+            logit(a.lq, sm.lq[sqp], nk);
+        } else {
+            kq(a.k, sm.k[sk], 0);
+            logit(a.lb, sm.lb[ss], nk);
+            logit(a.lk, sm.lk[ss], nk + nl);
+        }
         // [t][dl] tensors of one value per (token, output dim): v, and the gates
         auto vrow = [&](const void *base, uint4 *dstv, int ibase) {
             const char *src = static_cast<const char *>(base) + (row0 * Dv + d0) * 2;
@@ -354,21 +408,22 @@ __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB,
                 }
             }
         };
-        vrow(a.v, sm.v[ss], 2 * nk + 3 * nl);
-        if constexpr (TP) {
-            vrow(a.gk, sm.gk[ss], 2 * nk + 3 * nl + nv);
-            vrow(a.gq, sm.gq[sqp], 2 * nk + 3 * nl + 2 * nv);
+        if constexpr (QS) {
+            if constexpr (TP) vrow(a.gq, sm.gq[sqp], nk + nl);
+        } else {
+            vrow(a.v, sm.v[ss], nk + 2 * nl);
+            if constexpr (TP) vrow(a.gk, sm.gk[ss], nk + 2 * nl + nv);
         }
     } else {
         const size_t row0 = (size_t)b * T;
-        // K and Q rows: piece p of row t goes to slot p ^ (t mod pieces)
+        // K and Q rows: slot p of row t takes piece p ^ kperm(t)
         auto kq = [&](const void *base, uint4 *tile, int ibase) {
             for (int ins = first_for(ibase, mw, NIW); ins < ibase + nk; ins += NIW) {
                 const int part = ins - ibase, s = part * 64 + lane;
                 if (s < C::KPIECES) {
                     const int t = s / C::KPC, p = s % C::KPC;
                     const int tc = min(t0 + t, T - 1);
-                    const int gp = p ^ (t & (C::KPC - 1));
+                    const int gp = p ^ kperm<DK>(t);
                     dma16(static_cast<const uint16_t *>(base) + ((row0 + tc) * H + h) * DK + 8 * gp,
                           at(tile + part * 64));
                 }
@@ -388,11 +443,14 @@ __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB,
                 }
             }
         };
-        kq(a.k, sm.k[skq], 0);
-        kq(a.q, sm.q[skq], nk);
-        logit(a.lb, sm.lb[ss], 2 * nk);
-        logit(a.lk, sm.lk[ss], 2 * nk + nl);
-        logit(a.lq, sm.lq[sqp], 2 * nk + 2 * nl);
+        if constexpr (QS) {
+            kq(a.q, sm.q[sq], 0);
+            logit(a.lq, sm.lq[sqp], nk);
+        } else {
+            kq(a.k, sm.k[sk], 0);
+            logit(a.lb, sm.lb[ss], nk);
+            logit(a.lk, sm.lk[ss], nk + nl);
+        }
         auto vrow = [&](const void *base, uint4 *dstv, int ibase) {
             for (int ins = first_for(ibase, mw, NIW); ins < ibase + nv; ins += NIW) {
                 const int part = ins - ibase, s = part * 64 + lane;
@@ -405,14 +463,15 @@ __device__ __forceinline__ void issue_chunk(const LayerArgs &a, PSmem<DK, J, DB,
                 }
             }
         };
-        vrow(a.v, sm.v[ss], 2 * nk + 3 * nl);
-        if constexpr (TP) {
-            vrow(a.gk, sm.gk[ss], 2 * nk + 3 * nl + nv);
-            vrow(a.gq, sm.gq[sqp], 2 * nk + 3 * nl + 2 * nv);
+        if constexpr (QS) {
+            if constexpr (TP) vrow(a.gq, sm.gq[sqp], nk + nl);
+        } else {
+            vrow(a.v, sm.v[ss], nk + 2 * nl);
+            if constexpr (TP) vrow(a.gk, sm.gk[ss], nk + 2 * nl + nv);
         }
     }
-    if constexpr (NT) {
-        constexpr int ib = 2 * nk + 3 * nl + nv, np = (C::PPIECES + 63) / 64;
+    if constexpr (NT && !QS) {
+        constexpr int ib = nk + 2 * nl + nv, np = (C::PPIECES + 63) / 64;
         for (int ins = first_for(ib, mw, NIW); ins < ib + np; ins += NIW) {
             const int part = ins - ib, s = part * 64 + lane;
             if (s < C::PPIECES) dma16(pred + (size_t)t0 * C::N + 4 * s, at(sm.pw[sqp] + part * 64));
@@ -493,10 +552,8 @@ __device__ __forceinline__ void pipe_coords(int id, int ndb, int nheads, int &db
     }
 }
 
-// LDS (over 60 KB a block) allows at most two blocks on a compute unit, so at
-// most two waves share a SIMD: the compiler may use every register for that.
 template <int DK, int J, int DB, int MD, int NH>
-__global__ __launch_bounds__(512)
+__global__ __launch_bounds__(64 * (PCfg<DK, J, DB>::NW + 1 + NH))
 void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
     using C = PCfg<DK, J, DB>;
     constexpr int IT = C::IT, N = C::N, NW = C::NW, JP = C::JP;
@@ -515,14 +572,14 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
     const int NCH = (T + kC - 1) / kC;
     const bool seq = (w == NW);
     // Roles: waves 0 .. NW-1 hold the state tiles (matrix-core products);
-    // wave NW is the sequential wave; with NH > 0, waves NW+1 .. NW+NH do the
-    // per-chunk bookkeeping (transfers, priors, input prep, outputs), which the
-    // tile waves do themselves when NH = 0.
+    // wave NW is the sequential wave; with NH > 0, wave NW+1 forms the chunks' Gram
+    // matrices and waves NW+2 .. NW+NH do the per-chunk bookkeeping (transfers,
+    // priors, input prep, outputs); the tile waves do both when NH = 0.
     const bool tile = w < NW;
-    const bool book = NH == 0 ? tile : w > NW;        // this wave does the bookkeeping
-    constexpr int NBW = NH == 0 ? NW : NH;            // bookkeeping waves
+    const bool book = NH == 0 ? tile : w > NW + 1;    // this wave does the bookkeeping
+    constexpr int NBW = NH == 0 ? NW : NH - 1;        // bookkeeping waves
     constexpr int NBT = 64 * NBW;                     // bookkeeping threads
-    const int bw = NH == 0 ? w : w - (NW + 1);        // index among them
+    const int bw = NH == 0 ? w : w - (NW + 2);        // index among them
     // The compiler cannot bound bt (the wave index comes from readfirstlane), so
     // loops strided by NBT count 0 .. ceil(n / NBT) from bt and stop at n: a
     // trip count it can see, and fully unrolled loops.
@@ -533,7 +590,7 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
     // items fall on different waves.  (Called only by bookkeeping threads, for
     // which 0 <= bt < NBT.)
     auto brot = [&](int k) { return (bt + (k % NBW) * 64) % NBT; };
-    // the wave that forms the Gram matrix of the next chunk for the sequential wave
+    // the wave that forms the chunks' Gram matrices
     const bool gwave = NH == 0 ? w == 1 % NW : w == NW + 1;
     // Newton mode: this block's predictions, [NCH * kC][N] fp32
     float *const pred = NT ? na.pred + ((size_t)hh * (Dv / DB) + db) * NCH * kC * N : nullptr;
@@ -549,7 +606,7 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
         qs = near || met || sweeps + 1 >= na.max_iters;
     };
 
-    // ---- matrix-core wave state: W^T tile rows 16 it + 4 lg + r, column col
+    // ---- matrix-core wave state: W^T tile rows krow(it, lg) + r, column col
     const int col = 16 * (seq ? 0 : w) + tl;
     const int jc = col / DB, dc = d0 + col % DB;
     const size_t sbase = (((size_t)b * H + h) * J + jc) * DK * Dv + dc;
@@ -568,16 +625,15 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
             // registers across the sweeps.
             int dv = Dv;
             asm volatile("" : "+s"(dv));
-            const float *src = a.state_in + sbase + (size_t)(4 * lg) * dv;
+            const float *src = a.state_in + sbase;
 #pragma unroll
             for (int it = 0; it < IT; ++it)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) W[it][r] = kWS * src[(size_t)(16 * it + r) * dv];
+                for (int r = 0; r < 4; ++r) W[it][r] = kWS * src[(size_t)(krow<DK>(it, lg) + r) * dv];
         }
     };
     load_state();
-    floatx4 Yacc = {0.f, 0.f, 0.f, 0.f}, Xacc = Yacc;
-    short4v chi = {0, 0, 0, 0}, clo = chi, ghi = chi, glo = chi;
+    floatx4 Yacc = {0.f, 0.f, 0.f, 0.f};
 
     // ---- sequential wave identity: lanes of one output dim are adjacent
     const int sl = lane;
@@ -625,29 +681,74 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
         } else {
 #pragma unroll
             for (int s = 0; s < DK / 32; ++s) {
-                const bf16x8 av = __builtin_bit_cast(bf16x8, frag32<DK>(tile, tl, lg, s));
+                const bf16x8 av = __builtin_bit_cast(bf16x8, tile8<DK>(tile, tl, 4 * s + lg));
                 acc = mfma32(av, whi[s], acc);
                 acc = mfma32(av, wlo[s], acc);
             }
         }
         return acc;
     };
-    // rows(x) . rows(y)^T for two 16-row tiles (Gram-type product), exact products
-    auto gram = [&](const uint4 *x, const uint4 *y) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    // a 16-row tile as the operand of a Gram product
+    struct Rows {
+        bf16x8 x[IT / 2 > 0 ? IT / 2 : 1];
+        short4v y;
+    };
+    auto load_rows = [&](const uint4 *tile) {
+        Rows o;
         if constexpr (DK == 16) {
-            const short4v ax = __builtin_bit_cast(short4v, tile4<DK>(x, tl, 4 * lg));
-            const short4v ay = __builtin_bit_cast(short4v, tile4<DK>(y, tl, 4 * lg));
-            acc = mfma16(ax, ay, acc);
+            o.y = __builtin_bit_cast(short4v, tile4<DK>(tile, tl, 4 * lg));
         } else {
 #pragma unroll
-            for (int s = 0; s < DK / 32; ++s) {
-                const bf16x8 ax = __builtin_bit_cast(bf16x8, frag32<DK>(x, tl, lg, s));
-                const bf16x8 ay = __builtin_bit_cast(bf16x8, frag32<DK>(y, tl, lg, s));
-                acc = mfma32(ax, ay, acc);
-            }
+            for (int s = 0; s < DK / 32; ++s)
+                o.x[s] = __builtin_bit_cast(bf16x8, tile8<DK>(tile, tl, 4 * s + lg));
+        }
+        return o;
+    };
+    // rows(x) . rows(y)^T, exact products
+    auto gram = [&](const Rows &x, const Rows &y) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (DK == 16) {
+            acc = mfma16(x.y, y.y, acc);
+        } else {
+#pragma unroll
+            for (int s = 0; s < DK / 32; ++s) acc = mfma32(x.x[s], y.x[s], acc);
         }
         return acc;
+    };
+    // The Gram matrices of chunk m, formed once per block (parity m & 1).  For the
+    // sequential wave, negated: G_m = K_m K_m^T with its first subdiagonal, and
+    // the columns of G'_m = K_{m+1} K_m^T that belong to the chunk's last four
+    // tokens.  Lane (tl, lg) of an accumulator holds rows 4 lg .. 4 lg + 3 of
+    // column tl.  For the tile waves, as A operands from the accumulators of their
+    // transposes: G'_m (rows t of chunk m + 1, depth s) and, with qs, tril(A_m),
+    // A_m = Q_m K_m^T (slot m mod 3).
+    auto chunk_grams = [&](int m, bool qs) {
+        const int pr = m & 1;
+        const Rows km = load_rows(sm.k[m % kRingK]), kn = load_rows(sm.k[(m + 1) % kRingK]);
+        const Rows qm = load_rows(sm.q[m % kRingQ]);
+        const floatx4 gi = gram(km, km);
+        const floatx4 gt = gram(km, kn);   // [s = 4 lg + r][t = tl] (last chunk: not used)
+        const floatx4 at = gram(km, qm);   // [s = 4 lg + r][t = tl]
+        *reinterpret_cast<float4 *>(&sm.g[pr][kC * 4 * lg + 4 * tl]) =
+            make_float4(-gi[0], -gi[1], -gi[2], -gi[3]);
+        const int nx = tl + 1;
+        const float lo = nx & 1 ? gi[1] : gi[0], hi = nx & 1 ? gi[3] : gi[2];
+        if (nx >> 2 == lg) sm.gsub[pr][tl] = -(nx & 2 ? hi : lo);
+        auto put = [&](uint4 *dst, float x0, float x1, float x2, float x3) {
+            short4v h, l;
+            split4v(x0, x1, x2, x3, h, l);
+            const uint2 hu = __builtin_bit_cast(uint2, h), lu = __builtin_bit_cast(uint2, l);
+            dst[lane] = make_uint4(hu.x, hu.y, lu.x, lu.y);
+        };
+        put(sm.ga[pr], gt[0], gt[1], gt[2], gt[3]);
+        if (lg == kC / 4 - 1) {
+            // block 4 (s - 12) + t / 4, row t % 4
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sm.gx[pr][16 * r + tl] = -gt[r];
+        }
+        if (qs)
+            put(sm.qa[m % 3], 4 * lg <= tl ? at[0] : 0.f, 4 * lg + 1 <= tl ? at[1] : 0.f,
+                4 * lg + 2 <= tl ? at[2] : 0.f, 4 * lg + 3 <= tl ? at[3] : 0.f);
     };
     // Per-chunk bookkeeping works on groups of four consecutive columns (or
     // output dims), so that every thread makes one round trip to LDS.
@@ -922,36 +1023,35 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
         }
     };
     // Backward support: the state before chunk 2 m, unscaled, into
-    // ckpt [B, H, ceil(T / 32), Dv, J, Dk] (rows 16 it + 4 lg .. + 3 of column col)
+    // ckpt [B, H, ceil(T / 32), Dv, J, Dk] (rows krow(it, lg) .. + 3 of column col)
     auto store_ckpt = [&](int m) {
         static_assert(kBwdChunk == 2 * kC, "checkpoints every second chunk");
         const int NC2 = (T + 2 * kC - 1) / (2 * kC);
         float *dst = a.ckpt + ((((size_t)b * H + h) * NC2 + m) * Dv + dc) * J * DK +
-                     (size_t)jc * DK + 4 * lg;
+                     (size_t)jc * DK;
 #pragma unroll
         for (int it = 0; it < IT; ++it)
-            *reinterpret_cast<float4 *>(dst + 16 * it) =
+            *reinterpret_cast<float4 *>(dst + krow<DK>(it, lg)) =
                 make_float4(kInvWS * W[it][0], kInvWS * W[it][1], kInvWS * W[it][2],
                             kInvWS * W[it][3]);
     };
-    // W += K_m^T C_m and Y += tril(A_m) C_m (C_m split in chi/clo); then
-    // stage pi^q * Y of chunk m
+    // W += K_m^T C_m and Y += tril(A_m) C_m (C_m split into a bf16 high part and
+    // residual); then stage pi^q * Y of chunk m
     auto finish_chunk = [&](int m, bool qs) {
-        const int rs = m % kRingKQ, pr = m & 1;
+        const int rk = m % kRingK, pr = m & 1;
+        const float4 c4 = *reinterpret_cast<const float4 *>(&sm.c[pr][C::prow(col)][4 * lg]);
+        short4v chi, clo;
+        split4v(c4.x, c4.y, c4.z, c4.w, chi, clo);
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            // A operand K^T: lane (tl, lg) needs K[4 lg + mm][16 it + tl], mm = 0..3
-            const short4v ak = tile_tr<DK>(sm.k[rs], it, tl, lg);
+            const short4v ak = tile_tr<DK>(sm.k[rk], it, tl, lg);
             W[it] = mfma16(ak, chi, W[it]);
             W[it] = mfma16(ak, clo, W[it]);
         }
         if (!qs) return;   // (Newton: a sweep without the query side)
-        // (K_m Q_m^T)[s][t] in accumulator layout is lane (t = tl, s = 4 lg + r):
-        // exactly the A operand of tril(A_m) C_m, A_m = Q_m K_m^T
-        const floatx4 at = gram(sm.k[rs], sm.q[rs]);
-        short4v ahi, alo;
-        split4v(4 * lg <= tl ? at[0] : 0.f, 4 * lg + 1 <= tl ? at[1] : 0.f,
-                4 * lg + 2 <= tl ? at[2] : 0.f, 4 * lg + 3 <= tl ? at[3] : 0.f, ahi, alo);
+        const uint4 qa = sm.qa[m % 3][lane];
+        const short4v ahi = __builtin_bit_cast(short4v, make_uint2(qa.x, qa.y));
+        const short4v alo = __builtin_bit_cast(short4v, make_uint2(qa.z, qa.w));
         Yacc = mfma16(ahi, chi, Yacc);
         Yacc = mfma16(ahi, clo, Yacc);
         Yacc = mfma16(alo, chi, Yacc);
@@ -980,9 +1080,8 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
                 } else {
 #pragma unroll
                     for (int s = 0; s < DK / 32; ++s) {
-                        const uint2 x0 = *reinterpret_cast<const uint2 *>(row + 32 * s + 4 * lg);
-                        const uint2 x1 = *reinterpret_cast<const uint2 *>(row + 32 * s + 16 + 4 * lg);
-                        const bf16x8 av = __builtin_bit_cast(bf16x8, make_uint4(x0.x, x0.y, x1.x, x1.y));
+                        const bf16x8 av = __builtin_bit_cast(
+                            bf16x8, *reinterpret_cast<const uint4 *>(row + 32 * s + 8 * lg));
                         acc = mfma32(av, whi[s], acc);
                         acc = mfma32(av, wlo[s], acc);
                     }
@@ -1003,252 +1102,271 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
         while (!done) {
             ++sweeps;
             float dmax = 0.f, pmax = 0.f;   // Newton: largest change, largest prediction
-            // Exact mode: the per-token inputs of the next chunk and the first row
-            // of its Gram matrix, read while the matrix-core waves form its
-            // predictions (between the two barriers), off the critical path.
+            // The per-token inputs of the next chunk, read a chunk ahead, off the
+            // critical path.  Exact: beta and log2(e) times the key-prior logit.
             // Temporal: lkvN holds g^k pi^k and gsN 1 - g^k of the key prior
             // (1 - g^k) r_{t-1} + g^k pi^k (App. B.3); rprev is r_{t-1} of this
-            // lane's column, carried from chunk to chunk.
-            float vvN[kC], lkvN[kC], bevN[kC], growN[kC], gsN[TP ? kC : 1];
+            // lane's column, carried from chunk to chunk.  Newton: g, beta r delta
+            // and the previous sweep's predictions.
+            float lkvN[kC], bevN[kC], gsN[TP ? kC : 1], poldN[NT ? kC : 1];
+            // D: v - pred of the current chunk's tokens (scaled; Newton: -pred), four
+            // tokens a register group, in the accumulators of the 4x4 products; X:
+            // the next chunk's, less B.
+            floatx4 D[kC / 4], X[kC / 4];
             float rprev = 0.f;
             if constexpr (TP) {
                 if (bact)
                     rprev = a.prior_in ? a.prior_in[(((size_t)b * H + h) * 2 * J + bj) * Dv + d0 + bdl]
                                        : 1.f / J;
             }
-            auto fetch_inputs = [&](int prn) {
-                // 16-byte reads: few enough to be in flight together
-                const float4 *sq4 = reinterpret_cast<const float4 *>(sm.sq[prn][C::srow(bcol)]);
-                const float4 *vs4 = reinterpret_cast<const float4 *>(sm.vs[prn][bdl]);
-                const float4 *g4 = reinterpret_cast<const float4 *>(sm.g[prn][0]);
+            // part i of 4 (four tokens) of the inputs of chunk m; X starts at s v
+            auto fetch_inputs = [&](int m, int i) {
+                const int prn = m & 1;
+                if constexpr (NT) {
+                    const float *po = reinterpret_cast<const float *>(sm.pw[m % kRingQP]);
 #pragma unroll
-                for (int i = 0; i < kC / 2; ++i) {
-                    const float4 x = sq4[i];
-                    bevN[2 * i] = x.x, lkvN[2 * i] = x.y, bevN[2 * i + 1] = x.z, lkvN[2 * i + 1] = x.w;
-                }
+                    for (int t = 4 * i; t < 4 * i + 4; ++t) {
+                        bevN[t] = sm.beta[prn][t][bcol];
+                        lkvN[t] = sm.lks[prn][t][bcol];
+                        poldN[t] = po[t * N + bcol];
+                    }
+                    X[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+                } else {
+                    const float4 *sq4 = reinterpret_cast<const float4 *>(sm.sq[prn][C::srow(bcol)]);
 #pragma unroll
-                for (int i = 0; i < kC / 4; ++i) {
-                    const float4 x = vs4[i], y = g4[i];
-                    vvN[4 * i] = x.x, vvN[4 * i + 1] = x.y, vvN[4 * i + 2] = x.z, vvN[4 * i + 3] = x.w;
-                    growN[4 * i] = y.x, growN[4 * i + 1] = y.y, growN[4 * i + 2] = y.z, growN[4 * i + 3] = y.w;
+                    for (int u = 2 * i; u < 2 * i + 2; ++u) {
+                        const float4 x = sq4[u];
+                        bevN[2 * u] = x.x, lkvN[2 * u] = x.y, bevN[2 * u + 1] = x.z, lkvN[2 * u + 1] = x.w;
+                    }
+                    const float4 x = *reinterpret_cast<const float4 *>(&sm.vs[prn][bdl][4 * i]);
+                    X[i] = floatx4{x.x, x.y, x.z, x.w};
                 }
                 if constexpr (TP) {
-                    const float4 *gs4 = reinterpret_cast<const float4 *>(sm.gs[prn][bdl]);
-#pragma unroll
-                    for (int i = 0; i < kC / 4; ++i) {
-                        const float4 x = gs4[i];
-                        gsN[4 * i] = x.x, gsN[4 * i + 1] = x.y, gsN[4 * i + 2] = x.z, gsN[4 * i + 3] = x.w;
-                    }
+                    const float4 x = reinterpret_cast<const float4 *>(sm.gs[prn][bdl])[i];
+                    gsN[4 * i] = x.x, gsN[4 * i + 1] = x.y, gsN[4 * i + 2] = x.z, gsN[4 * i + 3] = x.w;
                 }
             };
-            block_sync_lds();               // prologue: ring filled
-            block_sync_lds();               // prologue: P_0, G_0
-            if constexpr (!NT) fetch_inputs(0);
+            block_sync_lds();               // prologue: chunks 0 and 1 landed
+            block_sync_lds();               // prologue: their inputs staged; B_0, G_0, G'_0
+#pragma unroll
+            for (int i = 0; i < kC / 4; ++i) fetch_inputs(0, i);
+            block_sync_lds();               // prologue: chunk 2 landed
             for (int n = 0; n < NCH; ++n) {
                 const int pr = n & 1;
-                float grow[kC];
-                if constexpr (NT) {
+                // ---- the token recurrence of chunk n.  B_n first: the first token
+                // waits for it alone.
+                floatx4 B[kC / 4];
 #pragma unroll
-                    for (int u = 1; u < kC; ++u) grow[u] = sm.g[pr][0][u];
+                for (int i = 0; i < kC / 4; ++i) {
+                    const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[pr][C::prow(bcol)][4 * i]);
+                    B[i] = floatx4{p4.x, p4.y, p4.z, p4.w};
                 }
+                float gsub[kC], g[kC / 4];
+                const float gx = sm.gx[pr][lane];
+#pragma unroll
+                for (int i = 0; i < kC / 4; ++i) {
+                    const float4 x = *reinterpret_cast<const float4 *>(&sm.gsub[pr][4 * i]);
+                    gsub[4 * i] = x.x, gsub[4 * i + 1] = x.y, gsub[4 * i + 2] = x.z, gsub[4 * i + 3] = x.w;
+                    g[i] = sm.g[pr][64 * i + lane];
+                }
+                float lkv[kC], bev[kC], gs[TP ? kC : 1], pold[NT ? kC : 1];
+                floatx4 D0[kC / 4];   // for a rerun of the chunk
+#pragma unroll
+                for (int t = 0; t < kC; ++t) {
+                    // padding component of J = 3: no mass.  (Idle lanes run column
+                    // 0's tokens; their coefficients go to a row of their own.)
+                    lkv[t] = !NT && JP != J && bpad ? (TP ? 0.f : -INFINITY) : lkvN[t];
+                    bev[t] = bevN[t];
+                    if constexpr (TP) gs[t] = JP != J && bpad ? 0.f : gsN[t];
+                    if constexpr (NT) pold[t] = poldN[t];
+                }
+#pragma unroll
+                for (int i = 0; i < kC / 4; ++i) D[i] = D0[i] = X[i] - B[i];
+                // (the next chunk's inputs, all before token kEarly, whose
+                // coefficient is the first to go into X; past the end the other slot's
+                // old ones, not used)
+                auto prefetch = [&](int i) { fetch_inputs(n + 1, i); };
+                // The deferred updates of coefficient c of token s: the groups of
+                // this chunk that hold a later token (the one that holds token
+                // s + 2, the next to be read, first); then, for the last four tokens,
+                // the next chunk's.
+                auto defer = [&](auto tag, float c) {
+                    constexpr int s = decltype(tag)::value, own = kC / 4 - (s + 2) / 4;
+                    defer1<s, 0, own>(c, D, X, g, gx);
+                    defer1<s, 1, own>(c, D, X, g, gx);
+                    defer1<s, 2, own>(c, D, X, g, gx);
+                    defer1<s, 3, own>(c, D, X, g, gx);
+                    defer1<s, 4, own>(c, D, X, g, gx);
+                };
                 if constexpr (!NT) {
-                    // ---- B: the token recurrence of chunk n, in scaled units.
-                    // The softmax over j runs without subtracting its maximum: for
-                    // logits and errors of ordinary size its sum z stays far inside
-                    // the fp32 range.  Should z of some column and token leave
-                    // [2^-100, 2^100], the chunk is run again with the maximum
-                    // subtracted.  Inside that range a component whose term was
-                    // lost to underflow (true value below 2^-126) has r below
+                    // In scaled units.  The softmax over j runs without subtracting
+                    // its maximum: for logits and errors of ordinary size its sum z
+                    // stays far inside the fp32 range.  Should z of some column and
+                    // token leave [2^-100, 2^100], the chunk is run again with the
+                    // maximum subtracted.  Inside that range a component whose term
+                    // was lost to underflow (true value below 2^-126) has r below
                     // 2^-126 / 2^-100 = 2^-26, and no term exceeds 2^100, so
                     // beta delta times a term stays finite.
-                    float P[kC], vv[kC], lkv[kC], bev[kC], gs[TP ? kC : 1];
-#pragma unroll
-                    for (int t = 0; t < kC; ++t) {
-                        // padding component of J = 3: no mass; idle lanes: harmless
-                        vv[t] = vvN[t];
-                        lkv[t] = bpad ? (TP ? 0.f : -INFINITY) : lkvN[t];
-                        bev[t] = bact ? bevN[t] : 0.f;
-                        if constexpr (TP) gs[t] = bpad ? 0.f : gsN[t];
-                    }
-                    const float rprev0 = rprev;   // for a rerun of the chunk
-#pragma unroll
-                    for (int u = 1; u < kC; ++u) grow[u] = growN[u];
-                    auto load_pred = [&]() {
-#pragma unroll
-                        for (int t = 0; t < kC; t += 4) {
-                            const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[pr][C::prow(bcol)][t]);
-                            P[t] = p4.x, P[t + 1] = p4.y, P[t + 2] = p4.z, P[t + 3] = p4.w;
-                        }
-                    };
-                    load_pred();
-                    // Software-pipelined: token t updates only P[t+1] at once; its
-                    // other updates (P[u], u > t+1) run during token t+1, between
-                    // the exponential and the sum over j, where they fill the wait.
-                    // The scheduling barriers and the empty asm pins keep the compiler
-                    // from sinking them into the dependent chain of a later token.
-                    // The coefficients go out four tokens at a time; the branch on
-                    // whether r is wanted is taken once per chunk.
+                    // One wave issues about one vector instruction per 5.5 cycles,
+                    // dependent or not, and a change between the vector and the matrix
+                    // unit costs it some 7 more, so the loop is bound by its
+                    // instruction count: token t updates only the next token's d itself,
+                    // and c_{t-1}'s other updates go out as one batch of products while
+                    // token t's exponential is under way.  The other independent
+                    // instructions (reads of the next chunk's inputs among them) stand
+                    // where the cross-lane adds would wait for their operands.  The
+                    // coefficients go out four tokens at a time; the branch on what goes
+                    // to sm.r (R: 0 nothing, 1 r, 2 delta) is taken once per chunk.
                     auto run = [&](auto want) {
-                        constexpr bool R = decltype(want)::value;
+                        constexpr int R = decltype(want)::value;
                         // chk is the largest z and 1/z seen (one max3 per token):
                         // above 2^100 iff some z left [2^-100, 2^100]
-                        float chk = 0.f, cprev = 0.f, gprev[kC], cb[4];
-#pragma unroll
-                        for (int t = 0; t < kC; ++t) {
-                            // row t+1 of G from column t+2 on, in 16-byte reads
-                            float gnext[kC];
-#pragma unroll
-                            for (int q4 = (t + 2) / 4; q4 < kC / 4; ++q4) {
-                                const float4 x = *reinterpret_cast<const float4 *>(&sm.g[pr][t + 1][4 * q4]);
-                                gnext[4 * q4] = x.x, gnext[4 * q4 + 1] = x.y;
-                                gnext[4 * q4 + 2] = x.z, gnext[4 * q4 + 3] = x.w;
-                            }
-                            // The deferred updates of this token (c_{t-1} into P[u],
-                            // u > t) in four parts, one in each latency gap of the
-                            // dependent chain d, exponent, exp2, sum over j, 1 / z,
-                            // P[t+1]; the scheduling barriers keep every part in its
-                            // gap and the empty asm pins keep the compiler from
-                            // sinking the updates into a later token.
-                            auto defer = [&](int part) {
-                                if (t >= 1) {
-                                    const int F = kC - 1 - t;
-                                    const int lo = t + 1 + F * part / 4, hi = t + 1 + F * (part + 1) / 4;
-#pragma unroll
-                                    for (int u = lo; u < hi; ++u) {
-                                        P[u] = fmaf(gprev[u], cprev, P[u]);
-                                        asm volatile("" : "+v"(P[u]));
-                                    }
-                                }
-                            };
-                            const float d = vv[t] - P[t];
-                            const float bd = bev[t] * d;
+                        float chk = 0.f, cprev = 0.f, cb[4], d = D[0][0];
+                        // (an integer test on bits the compiler cannot trace back to a
+                        // float: the file is compiled without NaN semantics, and a NaN,
+                        // whose magnitude bits exceed those of 2^100, must fail it too)
+                        auto bad = [&]() {
+                            uint32_t chk_bits = __float_as_uint(chk);
+                            asm volatile("" : "+v"(chk_bits));
+                            return __builtin_amdgcn_ballot_w64(
+                                       bact && (chk_bits & 0x7fffffffu) > 0x71800000u) != 0;   // 2^100
+                        };
+                        auto token = [&](auto tag) {
+                            constexpr int t = decltype(tag)::value;
                             float ex;
                             if constexpr (TP)   // key prior (1 - g^k) r_{t-1} + g^k pi^k
-                                ex = fmaf(gs[t], rprev, lkv[t]) * __builtin_amdgcn_exp2f(-d * d);
+                                ex = __builtin_amdgcn_exp2f(-d * d);
                             else
                                 ex = __builtin_amdgcn_exp2f(fmaf(-d, d, lkv[t]));
                             __builtin_amdgcn_sched_barrier(0);
-                            defer(0);
+                            if constexpr (t >= 1 && t != kEarly) defer(IntTag<(t > 0 ? t - 1 : 0)>{}, cprev);
+                            __builtin_amdgcn_sched_barrier(0);
+                            const float bd = bev[t] * d;
+                            if constexpr (TP) ex *= fmaf(gs[t], rprev, lkv[t]);
+                            if constexpr (t % 3 == 1 && t < kEarly) prefetch(t / 3);
                             __builtin_amdgcn_sched_barrier(0);
                             float z = ex;
                             if constexpr (JP >= 2) z += dpp_mov<0xb1>(z);   // lane ^ 1
                             const float bdex = bd * ex;
-                            const float gb = t + 1 < kC ? grow[t + 1] * bdex : 0.f;
-                            __builtin_amdgcn_sched_barrier(0);
-                            defer(1);
                             __builtin_amdgcn_sched_barrier(0);
                             if constexpr (JP >= 4) z += dpp_mov<0x4e>(z);   // lane ^ 2
                             if constexpr (JP >= 8) z += dpp_mov<0x141>(z);  // other quad of 8
                             if constexpr (JP >= 16) z += dpp_mov<0x140>(z); // other half of 16
-                            __builtin_amdgcn_sched_barrier(0);
-                            defer(2);
-                            __builtin_amdgcn_sched_barrier(0);
                             const float iz = rcp_fast(z);
-                            __builtin_amdgcn_sched_barrier(0);
-                            defer(3);
-                            __builtin_amdgcn_sched_barrier(0);
-                            if (t + 1 < kC) P[t + 1] = fmaf(gb, iz, P[t + 1]);
                             const float cs = bdex * iz;                  // s c
+                            float dn = 0.f;
+                            if constexpr (t + 1 < kC) dn = fmaf(gsub[t], cs, D[(t + 1) / 4][(t + 1) % 4]);
                             cb[t & 3] = cs;
                             if ((t & 3) == 3)
                                 *reinterpret_cast<float4 *>(&sm.c[pr][C::prow(bsto)][t - 3]) =
                                     make_float4(cb[0], cb[1], cb[2], cb[3]);
-                            if constexpr (R) {
+                            if constexpr (R == 1) {
                                 const float rt = ex * iz;
-                                sm.r[pr][t][bsto] = dmode ? kInvWS * d : rt;
+                                sm.r[pr][t][bsto] = rt;
                                 if constexpr (TP) rprev = rt;
                             }
-                            chk = fmaxf(chk, fmaxf(z, iz));
+                            if constexpr (R == 2) sm.r[pr][t][bsto] = kInvS * d;
+                            chk = fmaxf(fmaxf(z, iz), chk);
+                            asm volatile("" : "+v"(chk));
                             cprev = cs;
-#pragma unroll
-                            for (int u = t + 2; u < kC; ++u) gprev[u] = grow[u], grow[u] = gnext[u];
-                        }
-                        // (an integer test on bits the compiler cannot trace back to a
-                        // float: the file is compiled without NaN semantics, and a NaN,
-                        // whose magnitude bits exceed those of 2^100, must fail it too)
-                        uint32_t chk_bits = __float_as_uint(chk);
-                        asm volatile("" : "+v"(chk_bits));
-                        const bool bad = (chk_bits & 0x7fffffffu) > 0x71800000u;   // 2^100
-                        if (__builtin_amdgcn_ballot_w64(bact && bad) != 0) {
-                            // some softmax sum left the range: the chunk again, maximum subtracted
-#pragma unroll
-                            for (int u = 1; u < kC; ++u) grow[u] = sm.g[pr][0][u];
-                            load_pred();
-                            if constexpr (TP) rprev = rprev0;
-#pragma unroll
-                            for (int t = 0; t < kC; ++t) {
-                                float gnext[kC];
-#pragma unroll
-                                for (int u = t + 2; u < kC; ++u) gnext[u] = sm.g[pr][t + 1][u];
-                                const float d = vv[t] - P[t];
-                                const float bd = bev[t] * d;
-                                const float e = TP ? (bpad ? -INFINITY : -d * d) : fmaf(-d, d, lkv[t]);
-                                float ex = __builtin_amdgcn_exp2f(e - group_max<JP>(e));
-                                if constexpr (TP) ex *= fmaf(gs[t], rprev, lkv[t]);
-                                const float iz = rcp_fast(group_sum<JP>(ex));
-                                const float cs = (bd * ex) * iz;
-#pragma unroll
-                                for (int u = t + 1; u < kC; ++u) P[u] = fmaf(grow[u], cs, P[u]);
-                                sm.c[pr][C::prow(bsto)][t] = cs;
-                                if constexpr (R) {
-                                    const float rt = ex * iz;
-                                    sm.r[pr][t][bsto] = dmode ? kInvWS * d : rt;
-                                    if constexpr (TP) rprev = rt;
-                                }
-#pragma unroll
-                                for (int u = t + 2; u < kC; ++u) grow[u] = gnext[u];
+                            d = dn;
+                        };
+                        // a token with the maximum subtracted
+                        auto slow = [&](auto tag) {
+                            constexpr int t = decltype(tag)::value;
+                            const float dd = D[t / 4][t % 4];
+                            const float bd = bev[t] * dd;
+                            const float e = TP ? (bpad ? -INFINITY : -dd * dd) : fmaf(-dd, dd, lkv[t]);
+                            float ex = __builtin_amdgcn_exp2f(e - group_max<JP>(e));
+                            if constexpr (TP) ex *= fmaf(gs[t], rprev, lkv[t]);
+                            const float iz = rcp_fast(group_sum<JP>(ex));
+                            const float cs = (bd * ex) * iz;
+                            // (token t + 1 takes it through the product here)
+                            if constexpr ((t + 2) / 4 != (t + 1) / 4)
+                                D[(t + 1) / 4] = mfma4<t>(g[(t + 1) / 4], cs, D[(t + 1) / 4]);
+                            defer(tag, cs);
+                            sm.c[pr][C::prow(bsto)][t] = cs;
+                            if constexpr (R == 1) {
+                                const float rt = ex * iz;
+                                sm.r[pr][t][bsto] = rt;
+                                if constexpr (TP) rprev = rt;
                             }
+                            if constexpr (R == 2) sm.r[pr][t][bsto] = kInvS * dd;
+                        };
+                        const float rprev0 = rprev;
+                        token(IntTag<0>{}), token(IntTag<1>{}), token(IntTag<2>{}), token(IntTag<3>{});
+                        token(IntTag<4>{}), token(IntTag<5>{}), token(IntTag<6>{}), token(IntTag<7>{});
+                        token(IntTag<8>{}), token(IntTag<9>{}), token(IntTag<10>{}), token(IntTag<11>{});
+                        defer(IntTag<kEarly - 1>{}, cprev);
+                        if (bad()) {   // (before the tile waves read these coefficients)
+#pragma unroll
+                            for (int i = 0; i < kC / 4; ++i) D[i] = D0[i];
+                            if constexpr (TP) rprev = rprev0;
+                            slow(IntTag<0>{}), slow(IntTag<1>{}), slow(IntTag<2>{}), slow(IntTag<3>{});
+                            slow(IntTag<4>{}), slow(IntTag<5>{}), slow(IntTag<6>{}), slow(IntTag<7>{});
+                            slow(IntTag<8>{}), slow(IntTag<9>{}), slow(IntTag<10>{}), slow(IntTag<11>{});
+                            d = D[kEarly / 4][0];
+                        }
+                        floatx4 De = D[kEarly / 4];
+                        De[0] = d;
+                        const float rprev1 = rprev;
+                        chk = 0.f;
+                        token(IntTag<12>{});
+                        // m(n): the coefficients of tokens 0 .. kEarly - 1 are published
+                        // (the last store is a token old by now)
+                        block_sync_lds();
+                        token(IntTag<13>{}), token(IntTag<14>{}), token(IntTag<15>{});
+                        defer(IntTag<15>{}, cprev);
+                        if (bad()) {
+                            D[kEarly / 4] = De;
+#pragma unroll
+                            for (int i = 0; i < kC / 4; ++i) prefetch(i);
+                            if constexpr (TP) rprev = rprev1;
+                            slow(IntTag<12>{}), slow(IntTag<13>{}), slow(IntTag<14>{}), slow(IntTag<15>{});
                         }
                     };
-                    if (TP || want_r) run(BoolTag<true>{});
-                    else run(BoolTag<false>{});
-                } else {
-                    // ---- B: forward substitution of the linearised recurrence
-                    // (eq. linearized) over chunk n; g clamped to [0, 2 / |k_t|^2]
-                    // unless disabled
-                    const float *po = reinterpret_cast<const float *>(sm.pw[n % kRingQP]);
-                    float P[kC], gc[kC], bb[kC], pold[kC];
-                    const float glo_t = na.clamp ? 0.f : -INFINITY;
-#pragma unroll
-                    for (int t = 0; t < kC; ++t) {
-                        P[t] = sm.p[pr][C::prow(bcol)][t];
-                        const float ghi_t = na.clamp ? 2.f * rcp_fast(sm.g[pr][t][t]) : INFINITY;
-                        gc[t] = fminf(fmaxf(sm.beta[pr][t][bcol], glo_t), ghi_t);
-                        bb[t] = sm.lks[pr][t][bcol];
-                        pold[t] = po[t * N + bcol];
+                    if constexpr (TP) {
+                        run(IntTag<1>{});
+                    } else {
+                        if (dmode) run(IntTag<2>{});
+                        else if (want_r) run(IntTag<1>{});
+                        else run(IntTag<0>{});
                     }
-#pragma unroll
-                    for (int t = 0; t < kC; ++t) {
-                        float gnext[kC];
-#pragma unroll
-                        for (int u = t + 2; u < kC; ++u) gnext[u] = sm.g[pr][t + 1][u];
-                        const float pt = P[t];
-                        const float x = fmaf(gc[t], pold[t] - pt, bb[t]);
-#pragma unroll
-                        for (int u = t + 1; u < kC; ++u) P[u] = fmaf(grow[u], x, P[u]);
+                } else {
+                    // Forward substitution of the linearised recurrence (eq.
+                    // linearized); g clamped to [0, 2 / |k_t|^2] unless disabled.
+                    // D holds -pred.
+                    const float glo_t = na.clamp ? 0.f : -INFINITY;
+                    float xprev = 0.f, d = D[0][0];
+                    auto token = [&](auto tag) {
+                        constexpr int t = decltype(tag)::value;
+                        // (sm.g holds -k_t . k_s)
+                        const float ghi_t = na.clamp ? -2.f * rcp_fast(sm.g[pr][64 * (t / 4) + 4 * t + t % 4])
+                                                     : INFINITY;
+                        const float gc = fminf(fmaxf(bev[t], glo_t), ghi_t);
+                        const float x = fmaf(gc, pold[t] + d, lkv[t]);
+                        if constexpr (t >= 1) defer(IntTag<(t > 0 ? t - 1 : 0)>{}, xprev);
+                        if constexpr (t % 3 == 1 && t < kEarly) prefetch(t / 3);
                         sm.c[pr][C::prow(bsto)][t] = x;
                         const int tok = n * kC + t;
                         if (bact) {
-                            pred[(size_t)tok * N + bcol] = pt;
+                            pred[(size_t)tok * N + bcol] = -d;
                             if (tok < T) {
-                                dmax = fmaxf(dmax, fabsf(pt - pold[t]));
-                                pmax = fmaxf(pmax, fabsf(pt));
+                                dmax = fmaxf(dmax, fabsf(d + pold[t]));
+                                pmax = fmaxf(pmax, fabsf(d));
                             }
                         }
-#pragma unroll
-                        for (int u = t + 2; u < kC; ++u) grow[u] = gnext[u];
-                    }
+                        if constexpr (t + 1 < kC) d = fmaf(gsub[t], x, D[(t + 1) / 4][(t + 1) % 4]);
+                        xprev = x;
+                        if constexpr (t == kEarly) block_sync_lds();   // m(n)
+                    };
+                    token(IntTag<0>{}), token(IntTag<1>{}), token(IntTag<2>{}), token(IntTag<3>{});
+                    token(IntTag<4>{}), token(IntTag<5>{}), token(IntTag<6>{}), token(IntTag<7>{});
+                    token(IntTag<8>{}), token(IntTag<9>{}), token(IntTag<10>{}), token(IntTag<11>{});
+                    token(IntTag<12>{}), token(IntTag<13>{}), token(IntTag<14>{}), token(IntTag<15>{});
+                    defer(IntTag<15>{}, xprev);
                 }
-                block_sync_lds();   // e(n): C_n published
-                if constexpr (!NT) {
-                    if (n + 1 < NCH) fetch_inputs(pr ^ 1);
-                    // i(n+1), P_{n+1} ready.  This wave has no LDS stores in
-                    // flight here, and nothing rewrites the slots it is reading
-                    // before i(n+2): its reads may land after the barrier.
-                    asm volatile("s_barrier" ::: "memory");
-                } else {
-                    block_sync_lds();   // i(n+1): P_{n+1} ready
-                }
+                block_sync_lds();   // e(n): C_n published, B_{n+1} and G_{n+1} ready
             }
             block_sync_lds();       // epilogue
             if constexpr (NT) {
@@ -1279,16 +1397,20 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
     }
 
     // The matrix-core side, one copy per role: with NH = 0 the tile waves also
-    // do the bookkeeping; with NH > 0 the tile waves and the helper waves run
-    // copies of their own that meet the same barriers.
+    // do the bookkeeping and the Gram matrices; with NH > 0 the tile waves, the
+    // Gram wave and the bookkeeping waves run copies of their own that meet the
+    // same barriers.
     if constexpr (NH == 0) {
-        constexpr bool DT = true, DBK = true;
+        constexpr bool DT = true, DBK = true, DG = true;
 #include "scan_pipe_mfma_side.inc"
     } else if (tile) {
-        constexpr bool DT = true, DBK = false;
+        constexpr bool DT = true, DBK = false, DG = false;
+#include "scan_pipe_mfma_side.inc"
+    } else if (gwave) {
+        constexpr bool DT = false, DBK = false, DG = true;
 #include "scan_pipe_mfma_side.inc"
     } else {
-        constexpr bool DT = false, DBK = true;
+        constexpr bool DT = false, DBK = true, DG = false;
 #include "scan_pipe_mfma_side.inc"
     }
 }
@@ -1305,11 +1427,14 @@ hipError_t launch_cfg(const LayerArgs &a, const NewtonArgs &na, hipStream_t stre
     const long blocks = (long)(a.Dv / DB) * a.H * a.B;
     // Enough blocks to put two on every compute unit (LDS permitting): their
     // waves hide each other's latencies, so the tile waves keep the
-    // bookkeeping.  Otherwise helper waves take it over.
-    // (the temporal form has more per-chunk bookkeeping: always three helpers)
+    // bookkeeping.  Otherwise helper waves take it over: the Gram wave and four
+    // for the rest.  (With three, the last of them reaches the chunk's middle
+    // barrier after the sequential wave: 145 against 139 us at B=4 H=8 T=2048
+    // D=64 J=4, 480 against 430 us at B=2 H=16 T=4096 D=128 J=4; six are 1%
+    // faster at that shape and 11% slower in the temporal form.)
     // (a block over 80 KB of LDS is never two to a compute unit: only the
     // variant with helpers is built for it)
-    constexpr int NH = MD == 2 ? 3 : (C::NW < 3 ? C::NW : 3);
+    constexpr int NH = 5;
     if constexpr (lds <= 80 * 1024) {
         if (blocks >= 512) {
             hipLaunchKernelGGL((scan_pipe_kernel<DK, J, DB, MD, 0>), dim3((unsigned)blocks),
