@@ -288,7 +288,9 @@ typedef struct swila_gated {
  *     J <= 4 and J * Dk <= 512; other calls return SWILA_EUNSUPPORTED.
  *   SWILA_ALGO_RECURRENT: the token-by-token scan (either input dtype, with
  *     or without temporal priors, J * Dk <= 1024).
- *   SWILA_ALGO_AUTO: CHUNK_EXACT where it applies, else RECURRENT.
+ *   SWILA_ALGO_AUTO: CHUNK_EXACT where it applies; with temporal priors the
+ *     chunk form on products that keep all 24 bits of their fp32 operands, for
+ *     bf16 inputs, J <= 4 and J * Dk <= 256; else RECURRENT.
  *   SWILA_ALGO_NEWTON returns SWILA_EUNSUPPORTED.
  * T == 0 copies the states.
  */

@@ -83,7 +83,8 @@ hipError_t launch_scan_direct(const LayerArgs &a, hipStream_t stream);
 // temporal form.
 hipError_t launch_scan_pipe(const LayerArgs &a, hipStream_t stream);
 // Gated SwiLA (App. B.4) in chunks of 16 tokens on the matrix cores: bf16
-// inputs, no temporal priors, J <= 4, J * Dk <= 256 (gated_chunk_supported).
+// inputs, J <= 4, J * Dk <= 512, with the temporal priors J * Dk <= 256
+// (gated_chunk_supported).
 bool gated_chunk_supported(const LayerArgs &a);
 hipError_t launch_scan_gated_chunk(const LayerArgs &a, hipStream_t stream);
 hipError_t launch_scan_pipe_temporal(const LayerArgs &a, hipStream_t stream);

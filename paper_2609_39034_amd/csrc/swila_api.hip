@@ -497,7 +497,7 @@ int swila_forward_gated(const swila_shape *shape, const swila_opts *opts, const 
         return fail(SWILA_EUNSUPPORTED,
                     "the gated form runs on SWILA_ALGO_CHUNK_EXACT or SWILA_ALGO_RECURRENT");
     const bool chunk_ok = swila::gated_chunk_supported(a);
-    if (opts->algo == SWILA_ALGO_CHUNK_EXACT && !chunk_ok)
+    if (opts->algo == SWILA_ALGO_CHUNK_EXACT && (!chunk_ok || temporal))
         return fail(SWILA_EUNSUPPORTED,
                     "the gated chunk form takes bf16 inputs without temporal priors, J <= 4 "
                     "and J * Dk <= 512 (J=%d, Dk=%d)",
