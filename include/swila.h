@@ -65,7 +65,12 @@ typedef struct swila_shape {
 enum swila_dtype { SWILA_F32 = 0, SWILA_BF16 = 1 };
 
 enum swila_algo {
-    SWILA_ALGO_AUTO = 0,        /* CHUNK_EXACT for bf16 inputs with J <= 8, else RECURRENT */
+    SWILA_ALGO_AUTO = 0,        /* CHUNK_EXACT for bf16 inputs with J <= 8, else RECURRENT;
+                                   for fp32 inputs with J <= 4 and J * Dk <= 256, where the
+                                   grid is small enough for it to be faster, the recurrence
+                                   16 tokens at a time on the matrix cores with products that
+                                   keep all 24 bits of their operands (every fp32 operand in
+                                   three bf16 parts) */
     SWILA_ALGO_RECURRENT = 1,   /* token-by-token scan on the vector ALUs */
     SWILA_ALGO_CHUNK_EXACT = 2, /* the same recurrence evaluated 16 tokens at a time with
                                    the Dk-long products on the matrix cores (bf16 inputs
@@ -241,8 +246,7 @@ typedef struct swila_temporal {
  * swila_forward with the temporal priors above.  The other arguments are those
  * of swila_forward (no workspace: SWILA_ALGO_NEWTON, whose linearisation is
  * that of the plain recurrence, returns SWILA_EUNSUPPORTED).  SWILA_ALGO_AUTO
- * picks the matrix-core chunk scan for bf16 inputs and the token-by-token scan
- * for fp32, as swila_forward does.  T == 0 copies state_in and prior_in (or
+ * picks as swila_forward does.  T == 0 copies state_in and prior_in (or
  * zeros and 1/J) to the outputs.
  */
 int swila_forward_temporal(const swila_shape *shape, const swila_opts *opts,
@@ -290,7 +294,8 @@ typedef struct swila_gated {
  *     or without temporal priors, J * Dk <= 1024).
  *   SWILA_ALGO_AUTO: CHUNK_EXACT where it applies; with temporal priors the
  *     chunk form on products that keep all 24 bits of their fp32 operands, for
- *     bf16 inputs, J <= 4 and J * Dk <= 256; else RECURRENT.
+ *     bf16 inputs, J <= 4 and J * Dk <= 256; fp32 inputs as in swila_forward;
+ *     else RECURRENT.
  *   SWILA_ALGO_NEWTON returns SWILA_EUNSUPPORTED.
  * T == 0 copies the states.
  */
@@ -316,9 +321,10 @@ int swila_decode_step_gated(const swila_shape *shape, const swila_opts *opts,
  * gradient of a scalar loss L through the forward, for training.  The paper
  * trains through the sequential evaluation and gives no backward formulas;
  * this is the chain rule of that forward, evaluated with fp32 values and
- * accumulation (with bf16 inputs the reverse scan's Dk-long products take fp32
- * operands as a bf16 high part and residual on the matrix cores; the final
- * pass multiplies in fp32 on the matrix cores).
+ * accumulation (the reverse scan's Dk-long products take fp32 operands on the
+ * matrix cores as a bf16 high part and residual with bf16 inputs, and as three
+ * bf16 parts, which keep all 24 bits, with fp32 inputs; the final pass multiplies
+ * in fp32 on the matrix cores).
  *   q, k, v, beta_logit, prior_k_logit, prior_q_logit, state_in: the forward's
  *              inputs, as in swila_forward (state_in NULL = zeros).
  *   grad_o:    dL/do [B,T,H,Dv], out_dtype; required when T > 0.
@@ -332,9 +338,8 @@ int swila_decode_step_gated(const swila_shape *shape, const swila_opts *opts,
  *              every 32 tokens and the per-token operands the reverse scan
  *              hands to the final pass, and is overwritten.
  * Every output, the workspace and the inputs are pairwise disjoint.  The
- * algorithm field of opts is ignored: the backward recomputes the forward
- * with the matrix-core chunk scan for bf16 inputs and the token-by-token scan
- * for fp32 inputs.  T == 0 copies grad_state_out (or zeros) to grad_state_in.
+ * algorithm field of opts is ignored: the backward recomputes the forward as
+ * SWILA_ALGO_AUTO does.  T == 0 copies grad_state_out (or zeros) to grad_state_in.
  */
 int swila_backward(const swila_shape *shape, const swila_opts *opts,
                    const void *q, const void *k, const void *v,

@@ -87,6 +87,12 @@ hipError_t launch_scan_pipe(const LayerArgs &a, hipStream_t stream);
 // (gated_chunk_supported).
 bool gated_chunk_supported(const LayerArgs &a);
 hipError_t launch_scan_gated_chunk(const LayerArgs &a, hipStream_t stream);
+// The same kernel for fp32 inputs (plain, temporal and gated forms), with every
+// fp32 operand in three bf16 parts: J <= 4, J * Dk <= 256, no backward support.
+bool chunk_f32_supported(const LayerArgs &a);
+bool chunk_f32_preferred(const LayerArgs &a);
+hipError_t launch_scan_chunk_f32(const LayerArgs &a, hipStream_t stream);
+hipError_t launch_scan_chunk_f32_gated(const LayerArgs &a, hipStream_t stream);
 hipError_t launch_scan_pipe_temporal(const LayerArgs &a, hipStream_t stream);
 
 // Chunkwise quasi-Newton evaluation (App. D) on the same pipelined kernel;

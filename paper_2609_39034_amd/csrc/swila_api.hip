@@ -394,6 +394,8 @@ int swila_forward(const swila_shape *shape, const swila_opts *opts, const void *
         return newton_status(iters_out, st);
     }
     if (use_chunk(shape, opts)) return map_hip(swila::launch_scan_pipe(a, st), "chunk scan launch");
+    if (opts->algo == SWILA_ALGO_AUTO && swila::chunk_f32_preferred(a))
+        return map_hip(swila::launch_scan_chunk_f32(a, st), "chunk scan launch");
     return map_hip(swila::launch_scan_direct(a, st), "scan launch");
 }
 
@@ -454,6 +456,8 @@ int swila_forward_temporal(const swila_shape *shape, const swila_opts *opts, con
                        "prior state copy");
     }
     if (use_chunk(shape, opts)) return map_hip(swila::launch_scan_pipe(a, st), "chunk scan launch");
+    if (opts->algo == SWILA_ALGO_AUTO && swila::chunk_f32_preferred(a))
+        return map_hip(swila::launch_scan_chunk_f32(a, st), "chunk scan launch");
     return map_hip(swila::launch_scan_direct(a, st), "scan launch");
 }
 
@@ -521,6 +525,8 @@ int swila_forward_gated(const swila_shape *shape, const swila_opts *opts, const 
                        "prior state copy");
     }
     if (use_chunk) return map_hip(swila::launch_scan_gated_chunk(a, st), "gated chunk launch");
+    if (opts->algo == SWILA_ALGO_AUTO && swila::chunk_f32_preferred(a))
+        return map_hip(swila::launch_scan_chunk_f32(a, st), "gated chunk launch");
     return map_hip(swila::launch_scan_direct(a, st), "scan launch");
 }
 
