@@ -7,8 +7,8 @@
 //
 // 1. Forward recompute: delta_{tjd} of every token and the state W_n before
 //    every kBwdChunk-th token.  bf16 inputs run the matrix-core chunk scan with
-//    these outputs in place of o, fp32 inputs the token-by-token scan in its AX
-//    mode, as their forwards do.
+//    these outputs in place of o, fp32 inputs the chunk form for fp32 (AX) or the
+//    token-by-token scan in its AX mode, as their forwards do.
 //
 // 2. Reverse scan.  With G_{jd} = dL/dw_{t,jd}, per token in reverse:
 //      dy_j = do pi^q_j;  G_j += dy_j q_t;  dc_j = G_j . k_t
@@ -77,12 +77,14 @@ constexpr int chunk_tile_dims() { return J == 1 ? 16 : J == 3 ? 8 : 32 / J; }
 // the Gram products K K^T, K Q^T and the base K E + triu(K Q^T) Y in parallel;
 // one wave then runs the chunk's tokens in reverse, one lane per column (all J
 // components of DB output dims, J lanes adjacent), with the later tokens'
-// dpred folded in as deferred updates; last E += Q^T Y + K^T P.  With fp32
-// inputs every product is fp32 on the vector ALUs.  With bf16 inputs the
-// products run on the matrix cores: K and Q are exact in bf16, so K K^T and
+// dpred folded in as deferred updates; last E += Q^T Y + K^T P.  The products run
+// on the matrix cores.  With bf16 inputs K and Q are exact in bf16, so K K^T and
 // K Q^T are single products; E, Y, P and the Gram values are fp32, split into
 // a bf16 high part and a bf16 residual (about 2^-17 relative per operand,
-// fp32 accumulation).
+// fp32 accumulation).  With fp32 inputs every operand is split into three parts,
+// which keep its 24 bits, and six products are summed (B=2 H=4 T=509 Dk=32 Dv=64
+// J=4: the launch took 172 us with fp32 products on the vector ALUs, in five steps
+// between barriers).
 constexpr int kRC = 16;   // tokens per chunk of the reverse scan
 
 typedef short short4v __attribute__((ext_vector_type(4)));
@@ -91,33 +93,28 @@ typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 typedef float floatx2v __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// two fp32 values to packed bf16 (round to nearest; a in the low half), and
-// their residuals
+// two fp32 values to packed bf16 (round to nearest; a in the low half)
 __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2v{a, b}, bf16x2v));
 }
-__device__ __forceinline__ void split_pk(float a, float b, uint32_t &hi, uint32_t &lo) {
-    hi = pk_bf16(a, b);
-    lo = pk_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
-}
-// The k operand of a lane: M values (4 for the 16-deep product, 8 for the
-// 32-deep one) as bf16, or as high parts and residuals
-template <int M>
+// A lane's M depth values of an operand (4 for the 16-deep product, 8 for the
+// 32-deep one) as P bf16 parts: the values (exact when P = 1), and P - 1 residuals
+template <int M, int P>
 struct KOp {
-    uint32_t hi[M / 2], lo[M / 2];
+    uint32_t part[P][M / 2];
 };
-template <int M>
-__device__ __forceinline__ KOp<M> kop_exact(const float *x) {
-    KOp<M> o;
+template <int M, int P>
+__device__ __forceinline__ KOp<M, P> kop(const float *x) {
+    KOp<M, P> o;
 #pragma unroll
-    for (int m = 0; m < M / 2; ++m) o.hi[m] = pk_bf16(x[2 * m], x[2 * m + 1]), o.lo[m] = 0u;
-    return o;
-}
-template <int M>
-__device__ __forceinline__ KOp<M> kop_split(const float *x) {
-    KOp<M> o;
+    for (int m = 0; m < M / 2; ++m) {
+        float a = x[2 * m], b = x[2 * m + 1];
 #pragma unroll
-    for (int m = 0; m < M / 2; ++m) split_pk(x[2 * m], x[2 * m + 1], o.hi[m], o.lo[m]);
+        for (int p = 0; p < P; ++p) {
+            o.part[p][m] = pk_bf16(a, b);
+            a -= __uint_as_float(o.part[p][m] << 16), b -= __uint_as_float(o.part[p][m] & 0xffff0000u);
+        }
+    }
     return o;
 }
 __device__ __forceinline__ floatx4 mma(const uint32_t (&a)[2], const uint32_t (&b)[2], floatx4 c) {
@@ -129,6 +126,18 @@ __device__ __forceinline__ floatx4 mma(const uint32_t (&a)[4], const uint32_t (&
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
         __builtin_bit_cast(bf16x8, make_uint4(a[0], a[1], a[2], a[3])),
         __builtin_bit_cast(bf16x8, make_uint4(b[0], b[1], b[2], b[3])), c, 0, 0, 0);
+}
+
+// a b: the products of parts p and r with p + r below the larger part count
+template <int M, int PA, int PB>
+__device__ __forceinline__ floatx4 mmp(const KOp<M, PA> &a, const KOp<M, PB> &b, floatx4 c) {
+    constexpr int P = PA > PB ? PA : PB;
+#pragma unroll
+    for (int p = 0; p < PA; ++p)
+#pragma unroll
+        for (int r = 0; r < PB; ++r)
+            if (p + r < P) c = mma(a.part[p], b.part[r], c);
+    return c;
 }
 
 // J consecutive floats to global memory (16-byte stores where J allows).
@@ -149,10 +158,8 @@ __device__ __forceinline__ void st_row(float *p, const float (&v)[J]) {
 // IBF: bf16 inputs (the input dtype is fixed per instantiation, so that the
 // prefetch has one load variant; dL/do's dtype stays a run-time choice).
 //
-// Schedule.  fp32 inputs: per chunk, every thread stages the chunk, then the
-// Gram products, the base, the sequential wave's tokens, and the update of E,
-// each step between block barriers.  bf16 inputs: the staged inputs have two slots (chunk m in
-// slot m & 1) and three barriers per chunk:
+// Schedule.  The staged inputs have two slots (chunk m in slot m & 1) and a chunk
+// three barriers:
 //   A  the sequential wave runs chunk n's tokens; the other waves store
 //      chunk n+1's dv and the chunk pass's dpred of chunk n+1,
 //      stage chunk n-1 into the other slot from registers (storing its pi^q, c
@@ -172,12 +179,11 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     static_assert(NL <= 64 && kBwdChunk % kRC == 0 && N % 4 == 0, "one sequential wave");
     static_assert(DB % chunk_tile_dims<J>() == 0 || chunk_tile_dims<J>() % DB == 0,
                   "a block covers whole tiles of the chunk pass, or a part of one");
-    constexpr int NS = IBF ? 2 : 1;      // slots of the staged inputs
-    constexpr int KT = IBF ? 1 : DK;     // rows of K and Q transposed (fp32 products only)
+    constexpr int NS = 2;                // slots of the staged inputs
+    constexpr int PK = IBF ? 1 : 3, PE = IBF ? 2 : 3;   // parts of K and Q; of the fp32 operands
 
     __shared__ __align__(16) float sE[DK][CP];
     __shared__ __align__(16) float sK[NS][kRC][KP], sQ[NS][kRC][KP];   // rows t
-    __shared__ __align__(16) float sKt[KT][GP], sQt[KT][GP];           // the same, [i][t]
     __shared__ __align__(16) float sGkk[kRC][GP];                      // k_t . k_s (symmetric)
     __shared__ __align__(16) float sGkqT[kRC][GP];                     // [s][t] = k_t . q_s
     __shared__ __align__(16) float sBase[kRC][CP], sY[NS][kRC][CP], sP[NS][kRC][CP];
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     // owns, from a clamped row (the chunk's last token, the last item), with the
     // input dtype fixed at compile time: no load sits behind a branch (a load
     // there is waited for at the join); staging zeroes what lies past the end.
-    constexpr int F0 = IBF ? 64 : 0, FT = kThreads - F0;
+    constexpr int F0 = 64, FT = kThreads - F0;
     constexpr int NKQ = (kRC * (DK / 4) + FT - 1) / FT;
     constexpr int NSC = (kRC * DB + FT - 1) / FT;
     uint4 pk[NKQ] = {}, pq[NKQ] = {};   // (bf16: halves x and y)
@@ -295,8 +301,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
         const size_t pbase = ((size_t)b * H + h) * NC2 + t0 / kBwdChunk;
         return ((pbase * (Dv / CT) + d / CT) * kBwdChunk + t0 % kBwdChunk + t) * CT + d % CT;
     };
-    // chunk n's registers to slot sl: K, Q (and their transposes for the fp32
-    // products), delta, r, beta and dy = dL/do pi^q; and, from the same
+    // chunk n's registers to slot sl: K, Q, delta, r, beta and dy = dL/do pi^q; and, from the same
     // registers, the chunk pass's operands pi^q, c = beta r delta and dL/do (a
     // thread's J components are adjacent there)
     auto stage = [&](int n, int sl) {
@@ -309,10 +314,6 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
                 if (t >= nt) kv.x = kv.y = kv.z = kv.w = qv.x = qv.y = qv.z = qv.w = 0.0f;
                 *reinterpret_cast<float4 *>(&sK[sl][t][i]) = kv;
                 *reinterpret_cast<float4 *>(&sQ[sl][t][i]) = qv;
-                if constexpr (!IBF) {
-                    sKt[i][t] = kv.x, sKt[i + 1][t] = kv.y, sKt[i + 2][t] = kv.z, sKt[i + 3][t] = kv.w;
-                    sQt[i][t] = qv.x, sQt[i + 1][t] = qv.y, sQt[i + 2][t] = qv.z, sQt[i + 3][t] = qv.w;
-                }
             }
         }
 #pragma unroll
@@ -448,102 +449,49 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
             }
         }
     };
-    // Gram products of the chunk in slot sl: on the matrix cores (bf16 inputs;
-    // wave 2 K K^T, wave 3 K Q^T), else one (t, s) pair per thread
+    // Gram products of the chunk in slot sl: wave 2 K K^T, wave 3 K Q^T
     auto gram = [&](int sl) {
-        if constexpr (IBF) {
-            if (wv >= 2) {
-                // D[row][col] = sum_i A[row][i] K[col][i], A = K (D[t][s]) or Q
-                // (D[s][t] = k_t . q_s); lane: row / col tl, k slot lg
-                const float (*A)[KP] = wv == 2 ? sK[sl] : sQ[sl];
-                floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (wv >= 2) {
+            // D[row][col] = sum_i A[row][i] K[col][i], A = K (D[t][s]) or Q
+            // (D[s][t] = k_t . q_s); lane: row / col tl, k slot lg
+            const float (*A)[KP] = wv == 2 ? sK[sl] : sQ[sl];
+            floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i0 = 0; i0 < DK; i0 += KM * 4) {
-                    const KOp<KM> a8 = kop_exact<KM>(&A[tl][i0 + KM * lg]);
-                    const KOp<KM> b8 = kop_exact<KM>(&sK[sl][tl][i0 + KM * lg]);
-                    acc = mma(a8.hi, b8.hi, acc);
-                }
+            for (int i0 = 0; i0 < DK; i0 += KM * 4)
+                acc = mmp(kop<KM, PK>(&A[tl][i0 + KM * lg]), kop<KM, PK>(&sK[sl][tl][i0 + KM * lg]), acc);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (wv == 2) sGkk[4 * lg + r][tl] = acc[r];
-                    else sGkqT[4 * lg + r][tl] = acc[r];
-                }
+            for (int r = 0; r < 4; ++r) {
+                if (wv == 2) sGkk[4 * lg + r][tl] = acc[r];
+                else sGkqT[4 * lg + r][tl] = acc[r];
             }
-        } else {
-            const int t = tid / kRC, s2 = tid % kRC;
-            float gkk = 0.0f, gkq = 0.0f;
-#pragma unroll 4
-            for (int i = 0; i < DK; i += 4) {
-                const float4 kt = *reinterpret_cast<const float4 *>(&sK[sl][t][i]);
-                const float4 ks = *reinterpret_cast<const float4 *>(&sK[sl][s2][i]);
-                const float4 qs = *reinterpret_cast<const float4 *>(&sQ[sl][s2][i]);
-                gkk = fmaf(kt.x, ks.x, fmaf(kt.y, ks.y, fmaf(kt.z, ks.z, fmaf(kt.w, ks.w, gkk))));
-                gkq = fmaf(kt.x, qs.x, fmaf(kt.y, qs.y, fmaf(kt.z, qs.z, fmaf(kt.w, qs.w, gkq))));
-            }
-            sGkk[t][s2] = gkk;
-            sGkqT[s2][t] = gkq;
         }
     };
     // base_t = k_t . E + sum_{s>=t} (k_t . q_s) dy_s for the chunk in slot sl: a
-    // 16-column tile per wave on the matrix cores (bf16 inputs), else four
-    // tokens per thread
+    // 16-column tile per wave
     auto base = [&](int sl) {
-        if constexpr (IBF) {
-            for (int ct = wv; ct < NTC; ct += kThreads / 64) {
-                const int col = 16 * ct + tl;
-                const bool cv = col < N;
-                floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int ct = wv; ct < NTC; ct += kThreads / 64) {
+            const int col = 16 * ct + tl;
+            const bool cv = col < N;
+            floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i0 = 0; i0 < DK; i0 += KM * 4) {
-                    const KOp<KM> a8 = kop_exact<KM>(&sK[sl][tl][i0 + KM * lg]);   // K[t = tl][i]
-                    float ev[KM];
+            for (int i0 = 0; i0 < DK; i0 += KM * 4) {
+                float ev[KM];
 #pragma unroll
-                    for (int m = 0; m < KM; ++m) ev[m] = cv ? sE[i0 + KM * lg + m][col] : 0.0f;
-                    const KOp<KM> b8 = kop_split<KM>(ev);
-                    acc = mma(a8.hi, b8.hi, acc);
-                    acc = mma(a8.hi, b8.lo, acc);
-                }
-                // triu: A[t = tl][s = 4 lg + m] = k_t . q_s for s >= t, B = dy[s][col]
-                float gv[4], yv[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int s2 = 4 * lg + m;
-                    gv[m] = s2 >= tl ? sGkqT[s2][tl] : 0.0f;
-                    yv[m] = cv ? sY[sl][s2][col] : 0.0f;
-                }
-                const KOp<4> ga = kop_split<4>(gv), yb = kop_split<4>(yv);
-                acc = mma(ga.hi, yb.hi, acc);
-                acc = mma(ga.hi, yb.lo, acc);
-                acc = mma(ga.lo, yb.hi, acc);
-                if (cv) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) sBase[4 * lg + r][col] = acc[r];
-                }
+                for (int m = 0; m < KM; ++m) ev[m] = cv ? sE[i0 + KM * lg + m][col] : 0.0f;
+                acc = mmp(kop<KM, PK>(&sK[sl][tl][i0 + KM * lg]), kop<KM, PE>(ev), acc);   // K[t = tl][i]
             }
-        } else {
-            for (int e = tid; e < (kRC / 4) * N; e += kThreads) {
-                const int t4 = (e / N) * 4, col = e % N;
-                float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-                for (int i = 0; i < DK; ++i) {
-                    const float4 kv = *reinterpret_cast<const float4 *>(&sKt[i][t4]);
-                    const float ev = sE[i][col];
-                    acc[0] = fmaf(kv.x, ev, acc[0]);
-                    acc[1] = fmaf(kv.y, ev, acc[1]);
-                    acc[2] = fmaf(kv.z, ev, acc[2]);
-                    acc[3] = fmaf(kv.w, ev, acc[3]);
-                }
-                for (int s2 = t4; s2 < kRC; ++s2) {
-                    const float4 gq = *reinterpret_cast<const float4 *>(&sGkqT[s2][t4]);
-                    const float yv = sY[sl][s2][col];
-                    // only s >= t: token t4 + x takes s2 >= t4 + x
-                    acc[0] = fmaf(gq.x, yv, acc[0]);
-                    if (s2 >= t4 + 1) acc[1] = fmaf(gq.y, yv, acc[1]);
-                    if (s2 >= t4 + 2) acc[2] = fmaf(gq.z, yv, acc[2]);
-                    if (s2 >= t4 + 3) acc[3] = fmaf(gq.w, yv, acc[3]);
-                }
+            // triu: A[t = tl][s = 4 lg + m] = k_t . q_s for s >= t, B = dy[s][col]
+            float gv[4], yv[4];
 #pragma unroll
-                for (int x = 0; x < 4; ++x) sBase[t4 + x][col] = acc[x];
+            for (int m = 0; m < 4; ++m) {
+                const int s2 = 4 * lg + m;
+                gv[m] = s2 >= tl ? sGkqT[s2][tl] : 0.0f;
+                yv[m] = cv ? sY[sl][s2][col] : 0.0f;
+            }
+            acc = mmp(kop<4, PE>(gv), kop<4, PE>(yv), acc);
+            if (cv) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sBase[4 * lg + r][col] = acc[r];
             }
         }
     };
@@ -609,76 +557,51 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
         }
     };
     // E += Q^T Y + K^T P for the chunk in slot sl (E then holds the gradient
-    // from the tokens after the previous chunk): 16 x 16 tiles of E on the
-    // matrix cores (bf16 inputs), else four columns per thread
+    // from the tokens after the previous chunk), in 16 x 16 tiles of E
     auto update_e = [&](int sl) {
-        if constexpr (IBF) {
-            // tiles wv, wv + 4, ..., two at a time with every LDS read of both
-            // issued before their products (a clamped duplicate past the end
-            // is computed and not stored)
-            constexpr int NTL = (DK / 16) * NTC, NU = (NTL + 3) / 4;
+        // tiles wv, wv + 4, ..., two at a time with every LDS read of both
+        // issued before their products (a clamped duplicate past the end
+        // is computed and not stored)
+        constexpr int NTL = (DK / 16) * NTC, NU = (NTL + 3) / 4;
 #pragma unroll
-            for (int u0 = 0; u0 < NU; u0 += 2) {
-                constexpr int NP2 = NU > 1 ? 2 : 1;
-                floatx4 acc[NP2];
-                KOp<4> qa[NP2], ka[NP2], yb[NP2], pb[NP2];
+        for (int u0 = 0; u0 < NU; u0 += 2) {
+            constexpr int NP2 = NU > 1 ? 2 : 1;
+            floatx4 acc[NP2];
+            KOp<4, PK> qa[NP2], ka[NP2];
+            KOp<4, PE> yb[NP2], pb[NP2];
 #pragma unroll
-                for (int x = 0; x < NP2; ++x) {
-                    const int tile = min(wv + 4 * (u0 + x), NTL - 1);
-                    const int ti = tile / NTC, col = 16 * (tile % NTC) + tl;
-                    const bool cv = col < N;
-                    const int cc = cv ? col : 0;
+            for (int x = 0; x < NP2; ++x) {
+                const int tile = min(wv + 4 * (u0 + x), NTL - 1);
+                const int ti = tile / NTC, col = 16 * (tile % NTC) + tl;
+                const bool cv = col < N;
+                const int cc = cv ? col : 0;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[x][r] = cv ? sE[16 * ti + 4 * lg + r][cc] : 0.0f;
-                    // A = Q^T, K^T: rows i = 16 ti + tl, k = t = 4 lg .. + 3
-                    float qv[4], kv[4], yv[4], pv[4];
+                for (int r = 0; r < 4; ++r) acc[x][r] = cv ? sE[16 * ti + 4 * lg + r][cc] : 0.0f;
+                // A = Q^T, K^T: rows i = 16 ti + tl, k = t = 4 lg .. + 3
+                float qv[4], kv[4], yv[4], pv[4];
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        qv[m] = sQ[sl][4 * lg + m][16 * ti + tl];
-                        kv[m] = sK[sl][4 * lg + m][16 * ti + tl];
-                        yv[m] = cv ? sY[sl][4 * lg + m][cc] : 0.0f;
-                        pv[m] = cv ? sP[sl][4 * lg + m][cc] : 0.0f;
-                    }
-                    qa[x] = kop_exact<4>(qv), ka[x] = kop_exact<4>(kv);
-                    yb[x] = kop_split<4>(yv), pb[x] = kop_split<4>(pv);
+                for (int m = 0; m < 4; ++m) {
+                    qv[m] = sQ[sl][4 * lg + m][16 * ti + tl];
+                    kv[m] = sK[sl][4 * lg + m][16 * ti + tl];
+                    yv[m] = cv ? sY[sl][4 * lg + m][cc] : 0.0f;
+                    pv[m] = cv ? sP[sl][4 * lg + m][cc] : 0.0f;
                 }
-#pragma unroll
-                for (int x = 0; x < NP2; ++x) {
-                    acc[x] = mma(qa[x].hi, yb[x].hi, acc[x]);
-                    acc[x] = mma(qa[x].hi, yb[x].lo, acc[x]);
-                    acc[x] = mma(ka[x].hi, pb[x].hi, acc[x]);
-                    acc[x] = mma(ka[x].hi, pb[x].lo, acc[x]);
-                }
-#pragma unroll
-                for (int x = 0; x < NP2; ++x) {
-                    const int tile = wv + 4 * (u0 + x);
-                    const int ti = tile / NTC, col = 16 * (tile % NTC) + tl;
-                    if (u0 + x < NU && tile < NTL && col < N) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) sE[16 * ti + 4 * lg + r][col] = acc[x][r];
-                    }
-                }
+                qa[x] = kop<4, PK>(qv), ka[x] = kop<4, PK>(kv);
+                yb[x] = kop<4, PE>(yv), pb[x] = kop<4, PE>(pv);
             }
-        } else {
-            for (int e = tid; e < DK * (N / 4); e += kThreads) {
-                const int i = e / (N / 4), c4 = (e % (N / 4)) * 4;
-                float4 acc = *reinterpret_cast<const float4 *>(&sE[i][c4]);
 #pragma unroll
-                for (int t4 = 0; t4 < kRC; t4 += 4) {
-                    const float4 qv = *reinterpret_cast<const float4 *>(&sQt[i][t4]);
-                    const float4 kv = *reinterpret_cast<const float4 *>(&sKt[i][t4]);
-                    const float qa[4] = {qv.x, qv.y, qv.z, qv.w}, ka[4] = {kv.x, kv.y, kv.z, kv.w};
+            for (int x = 0; x < NP2; ++x) {
+                acc[x] = mmp(qa[x], yb[x], acc[x]);
+                acc[x] = mmp(ka[x], pb[x], acc[x]);
+            }
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const float4 y = *reinterpret_cast<const float4 *>(&sY[sl][t4 + x][c4]);
-                        const float4 p = *reinterpret_cast<const float4 *>(&sP[sl][t4 + x][c4]);
-                        acc.x = fmaf(qa[x], y.x, fmaf(ka[x], p.x, acc.x));
-                        acc.y = fmaf(qa[x], y.y, fmaf(ka[x], p.y, acc.y));
-                        acc.z = fmaf(qa[x], y.z, fmaf(ka[x], p.z, acc.z));
-                        acc.w = fmaf(qa[x], y.w, fmaf(ka[x], p.w, acc.w));
-                    }
+            for (int x = 0; x < NP2; ++x) {
+                const int tile = wv + 4 * (u0 + x);
+                const int ti = tile / NTC, col = 16 * (tile % NTC) + tl;
+                if (u0 + x < NU && tile < NTL && col < N) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sE[16 * ti + 4 * lg + r][col] = acc[x][r];
                 }
-                *reinterpret_cast<float4 *>(&sE[i][c4]) = acc;
             }
         }
     };
@@ -709,7 +632,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
             }
         }
     };
-    constexpr ITag<64> kF1{};               // the staging threads of the bf16 schedule
+    constexpr ITag<64> kF1{};               // the staging threads
     constexpr ITag<kThreads - 64> kN1{};
     constexpr ITag<0> kF0{};                // every thread
     constexpr ITag<kThreads> kN0{};
@@ -717,68 +640,47 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     constexpr ITag<kThreads - 128> kN2{};
 
 
-    if constexpr (IBF) {
-        if (NCH > 0) {
-            const int n0 = NCH - 1;
-            if (tid >= F0) {
-                fetch(n0);
-                stage(n0, n0 & 1);
-                if (n0 > 0) fetch(n0 - 1);
-            }
-            block_sync_lds();
-            gram(n0 & 1);
-            block_sync_lds();
-            base(n0 & 1);
-            for (int n = n0; n >= 0; --n) {
-                const int sl = n & 1;
-                block_sync_lds();   // A: the base of chunk n and E are complete
-                if (tid < 64) {
-                    tokens(sl);
-                } else {
-                    checkpoint(n, kF1, kN1);
-                    if (n < n0) {
-                        packs_dpred(n + 1, sl ^ 1, kF1, kN1);
-                        dv_store(n + 1, sl ^ 1, kF1, kN1);
-                    }
-                    if (n > 0) {
-                        stage(n - 1, sl ^ 1);
-                        if (n > 1) fetch(n - 2);   // lands during chunks n and n - 1
-                    }
+    if (NCH > 0) {
+        const int n0 = NCH - 1;
+        if (tid >= F0) {
+            fetch(n0);
+            stage(n0, n0 & 1);
+            if (n0 > 0) fetch(n0 - 1);
+        }
+        block_sync_lds();
+        gram(n0 & 1);
+        block_sync_lds();
+        base(n0 & 1);
+        for (int n = n0; n >= 0; --n) {
+            const int sl = n & 1;
+            block_sync_lds();   // A: the base of chunk n and E are complete
+            if (tid < 64) {
+                tokens(sl);
+            } else {
+                checkpoint(n, kF1, kN1);
+                if (n < n0) {
+                    packs_dpred(n + 1, sl ^ 1, kF1, kN1);
+                    dv_store(n + 1, sl ^ 1, kF1, kN1);
                 }
-                block_sync_lds();   // B: chunk n's dpred published
-                update_e(sl);
-                if (n > 0) gram(sl ^ 1);   // waves 2 and 3
-                if constexpr (NTC > 2) outputs(n, sl, kF0, kN0);
-                block_sync_lds();   // C: E now from the tokens after chunk n - 1
-                if (n > 0) base(sl ^ 1);   // waves 0 .. NTC - 1
-                // (with two column tiles, waves 2 and 3 store the outputs meanwhile)
-                if constexpr (NTC <= 2) {
-                    if (wv >= 2) outputs(n, sl, kF2, kN2);
+                if (n > 0) {
+                    stage(n - 1, sl ^ 1);
+                    if (n > 1) fetch(n - 2);   // lands during chunks n and n - 1
                 }
             }
-            // chunk 0's tokens ended before the last barrier B
-            packs_dpred(0, 0, kF0, kN0);
-            dv_store(0, 0, kF0, kN0);
+            block_sync_lds();   // B: chunk n's dpred published
+            update_e(sl);
+            if (n > 0) gram(sl ^ 1);   // waves 2 and 3
+            if constexpr (NTC > 2) outputs(n, sl, kF0, kN0);
+            block_sync_lds();   // C: E now from the tokens after chunk n - 1
+            if (n > 0) base(sl ^ 1);   // waves 0 .. NTC - 1
+            // (with two column tiles, waves 2 and 3 store the outputs meanwhile)
+            if constexpr (NTC <= 2) {
+                if (wv >= 2) outputs(n, sl, kF2, kN2);
+            }
         }
-    } else {
-        if (NCH > 0) fetch(NCH - 1);
-        for (int n = NCH - 1; n >= 0; --n) {
-            block_sync_lds();   // E is complete; the previous chunk's staging is consumed
-            checkpoint(n, kF0, kN0);
-            stage(n, 0);
-            block_sync_lds();
-            if (n > 0) fetch(n - 1);   // lands while this chunk computes
-            gram(0);
-            block_sync_lds();
-            base(0);
-            block_sync_lds();
-            if (tid < 64) tokens(0);
-            block_sync_lds();
-            update_e(0);
-            outputs(n, 0, kF0, kN0);
-            packs_dpred(n, 0, kF0, kN0);
-            dv_store(n, 0, kF0, kN0);
-        }
+        // chunk 0's tokens ended before the last barrier B
+        packs_dpred(0, 0, kF0, kN0);
+        dv_store(0, 0, kF0, kN0);
     }
     block_sync_lds();
     if (a.dstate) {
@@ -1181,8 +1083,10 @@ hipError_t launch_bwd_dk_j(const BackwardArgs &a, hipStream_t stream) {
     fa.delta_out = a.delta;
     fa.ckpt = a.wck;
     // bf16 inputs: the matrix-core chunk scan recomputes the forward; fp32 inputs
-    // take the token-by-token scan, as their forward does
-    hipError_t e = f.in_bf16 ? launch_scan_pipe(fa, stream) : launch_scan_direct_aux(fa, stream);
+    // take the chunk form or the token-by-token scan, as their forward does
+    hipError_t e = f.in_bf16                  ? launch_scan_pipe(fa, stream)
+                   : chunk_f32_preferred(fa) ? launch_scan_chunk_f32(fa, stream)
+                                             : launch_scan_direct_aux(fa, stream);
     if (e != hipSuccess) return e;
     // reverse scan: 64 sequential lanes per block (DB = 64 / JP output dims), or
     // half as many (and twice the blocks) while the grid would leave compute
