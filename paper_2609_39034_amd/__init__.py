@@ -129,28 +129,60 @@ def version() -> int:
     return load_library().swila_version()
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+class _Codes(dict):
+    """dtype -> enum swila_dtype, filled when torch is first needed."""
+
+    def get(self, dtype):
+        if not self:
+            torch = _torch()
+            self.update({torch.bfloat16: BF16, torch.float32: F32})
+        return dict.get(self, dtype)
+
+
+_CODES = _Codes()
 
 
 def _dtype_code(t):
+    code = _CODES.get(t.dtype)
+    if code is None:
+        raise TypeError("inputs must be float32 or bfloat16, got %s" % t.dtype)
+    return code
+
+
+def _new_output(v, q, out_dtype):
+    """An output of v's shape on q's device, in out_dtype (None: q's)."""
     torch = _torch()
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype == torch.float32:
-        return F32
-    raise TypeError("inputs must be float32 or bfloat16, got %s" % t.dtype)
+    if out_dtype is None and v.get_device() == q.get_device():
+        return torch.empty_like(v, memory_format=torch.contiguous_format)   # (the cheapest)
+    return q.new_empty(v.shape, dtype=out_dtype)
 
 
+# (Pointers and the stream go to ctypes as plain integers: the argument types of
+# load_library convert them, at half the cost of building c_void_p objects.)
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream_handle(stream):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    c = _torch()._C
+    try:
+        # torch.cuda.current_stream().cuda_stream without the Stream object
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    except AttributeError:
+        return _torch().cuda.current_stream().cuda_stream
 
 
 def _dev_tensor(t, name, dtype=None):
@@ -171,7 +203,7 @@ def _expect_shape(t, shape, name):
     size is reported before anything reaches the library."""
     if t is None or t is True or t is False:
         return
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
 
 
@@ -193,6 +225,21 @@ def _check_layer(tensors, decode, o=None, state_in=None, state_out=None):
     (B, H, T, Dk, Dv, J))."""
     q, v, lb = tensors[0], tensors[2], tensors[3]
     B, H, T, Dk, Dv, J = _layer_shapes(q, v, lb, decode=decode)
+    # One pass over everything that has to hold.  Only a call that fails it goes
+    # through the checks below, which name what is wrong.
+    key, val, log = ((B, H, Dk), (B, H, Dv), (B, H, J, Dv)) if decode else (
+        (B, T, H, Dk), (B, T, H, Dv), (B, T, H, J, Dv))
+    dt, w = q.dtype, (B, H, J, Dk, Dv)
+    code = _CODES.get(dt)
+    if code is not None:
+        for t, shape in zip(tensors, (key, key, val, log, log, log)):
+            if (t.shape != shape or t.dtype is not dt or not t.is_cuda or not t.is_contiguous()):
+                break
+        else:
+            if ((state_in is None or state_in.shape == w)
+                    and (state_out is None or state_out is True or state_out is False
+                         or state_out.shape == w) and (o is None or o.shape == val)):
+                return tensors, code, (B, H, T, Dk, Dv, J)
     expect = _input_shapes(B, H, T, Dk, Dv, J, decode)
     for t, n in zip(tensors, _IN_NAMES):
         _expect_shape(t, expect[n], n)
@@ -275,9 +322,8 @@ def forward(q, k, v, beta_logit, prior_k_logit, prior_q_logit, state_in=None, *,
         (q, k, v, beta_logit, prior_k_logit, prior_q_logit), False, o=o, state_in=state_in,
         state_out=state_out)
     _dev_tensor(state_in, "state_in", torch.float32)
-    odt = q.dtype if out_dtype is None else out_dtype
     if o is None:
-        o = torch.empty((B, T, H, Dv), device=q.device, dtype=odt)
+        o = _new_output(v, q, out_dtype)
     _dev_tensor(o, "o")
     if state_out is True:
         s_out = torch.empty((B, H, J, Dk, Dv), device=q.device, dtype=torch.float32)
@@ -411,9 +457,8 @@ def decode_step(q, k, v, beta_logit, prior_k_logit, prior_q_logit, state_in, *,
         state_out = state_in if state_in is not None else torch.empty(
             (B, H, J, Dk, Dv), device=q.device, dtype=torch.float32)
     _dev_tensor(state_out, "state_out", torch.float32)
-    odt = q.dtype if out_dtype is None else out_dtype
     if o is None:
-        o = torch.empty((B, H, Dv), device=q.device, dtype=odt)
+        o = _new_output(v, q, out_dtype)
     _dev_tensor(o, "o")
     opts = Opts(code, _dtype_code(o), ALGO_AUTO, 0, 0, 0.0, 0)
     _check(load_library().swila_decode_step(
@@ -430,12 +475,14 @@ def _temporal_args(gate_k_logit, gate_q_logit, prior_in, prior_out, code, gate_s
     for t, n in ((gate_k_logit, "gate_k_logit"), (gate_q_logit, "gate_q_logit")):
         if t is None:
             raise ValueError("%s is required" % n)
-        _expect_shape(t, gate_shape, n)
+        if t.shape != gate_shape:
+            _expect_shape(t, gate_shape, n)
     _expect_shape(prior_in, prior_shape, "prior_in")
     _expect_shape(prior_out, prior_shape, "prior_out")
     for t, n in ((gate_k_logit, "gate_k_logit"), (gate_q_logit, "gate_q_logit")):
         _dev_tensor(t, n)
-        if _dtype_code(t) != code:
+        if _CODES.get(t.dtype) != code:
+            _dtype_code(t)   # (raises for other types)
             raise TypeError("%s must have the dtype of q" % n)
     _dev_tensor(prior_in, "prior_in", torch.float32)
     if prior_out is True:
@@ -470,9 +517,8 @@ def forward_temporal(q, k, v, beta_logit, prior_k_logit, prior_q_logit, gate_k_l
     _dev_tensor(state_in, "state_in", torch.float32)
     tp, p_out = _temporal_args(gate_k_logit, gate_q_logit, prior_in, prior_out, code,
                                (B, T, H, Dv), (B, H, 2, J, Dv), q.device)
-    odt = q.dtype if out_dtype is None else out_dtype
     if o is None:
-        o = torch.empty((B, T, H, Dv), device=q.device, dtype=odt)
+        o = _new_output(v, q, out_dtype)
     _dev_tensor(o, "o")
     if state_out is True:
         s_out = torch.empty((B, H, J, Dk, Dv), device=q.device, dtype=torch.float32)
@@ -514,9 +560,8 @@ def decode_step_temporal(q, k, v, beta_logit, prior_k_logit, prior_q_logit, gate
         prior_out = prior_in if prior_in is not None else True
     tp, p_out = _temporal_args(gate_k_logit, gate_q_logit, prior_in, prior_out, code,
                                (B, H, Dv), (B, H, 2, J, Dv), q.device)
-    odt = q.dtype if out_dtype is None else out_dtype
     if o is None:
-        o = torch.empty((B, H, Dv), device=q.device, dtype=odt)
+        o = _new_output(v, q, out_dtype)
     _dev_tensor(o, "o")
     opts = Opts(code, _dtype_code(o), ALGO_AUTO, 0, 0, 0.0, 0)
     _check(load_library().swila_decode_step_temporal(
@@ -557,9 +602,8 @@ def forward_gated(q, k, v, beta_logit, prior_k_logit, prior_q_logit, decay_logit
     if temporal:
         tp, p_out = _temporal_args(gate_k_logit, gate_q_logit, prior_in, prior_out, code,
                                    (B, T, H, Dv), (B, H, 2, J, Dv), q.device)
-    odt = q.dtype if out_dtype is None else out_dtype
     if o is None:
-        o = torch.empty((B, T, H, Dv), device=q.device, dtype=odt)
+        o = _new_output(v, q, out_dtype)
     _dev_tensor(o, "o")
     if state_out is True:
         s_out = torch.empty((B, H, J, Dk, Dv), device=q.device, dtype=torch.float32)
@@ -605,9 +649,8 @@ def decode_step_gated(q, k, v, beta_logit, prior_k_logit, prior_q_logit, decay_l
             prior_out = prior_in if prior_in is not None else True
         tp, p_out = _temporal_args(gate_k_logit, gate_q_logit, prior_in, prior_out, code,
                                    (B, H, Dv), (B, H, 2, J, Dv), q.device)
-    odt = q.dtype if out_dtype is None else out_dtype
     if o is None:
-        o = torch.empty((B, H, Dv), device=q.device, dtype=odt)
+        o = _new_output(v, q, out_dtype)
     _dev_tensor(o, "o")
     opts = Opts(code, _dtype_code(o), ALGO_AUTO, 0, 0, 0.0, 0)
     _check(load_library().swila_decode_step_gated(
