@@ -86,6 +86,7 @@ constexpr int chunk_tile_dims() { return J == 1 ? 16 : J == 3 ? 8 : 32 / J; }
 // J=4: the launch took 172 us with fp32 products on the vector ALUs, in five steps
 // between barriers).
 constexpr int kRC = 16;   // tokens per chunk of the reverse scan
+constexpr int kRT = 512;  // threads of a reverse-scan block: the sequential wave and seven others
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -167,10 +168,10 @@ __device__ __forceinline__ void st_row(float *p, const float (&v)[J]) {
 //   B  E += Q_n^T Y_n + K_n^T P_n; waves 2 and 3 also the Gram products of
 //      chunk n-1
 //   C  the base of chunk n-1 from the new E (one wave per 16-column tile);
-//      chunk n's outputs on waves 2 and 3 when there are two tiles or fewer,
+//      chunk n's outputs on waves 2 and up when there are two tiles or fewer,
 //      else in B.
 template <int DK, int J, int DB, bool IBF>
-__global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a) {
+__global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
     constexpr int JP = J == 3 ? 4 : J;   // lanes per output dim (J = 3 padded)
     constexpr int N = J * DB;            // columns, col = j * DB + dd
     constexpr int NL = JP * DB;          // sequential lanes, lane = dd * JP + j
@@ -186,6 +187,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     __shared__ __align__(16) float sK[NS][kRC][KP], sQ[NS][kRC][KP];   // rows t
     __shared__ __align__(16) float sGkk[kRC][GP];                      // k_t . k_s (symmetric)
     __shared__ __align__(16) float sGkqT[kRC][GP];                     // [s][t] = k_t . q_s
+    __shared__ __align__(16) float sGsub[kRC];                         // k_t . k_{t-1}
     __shared__ __align__(16) float sBase[kRC][CP], sY[NS][kRC][CP], sP[NS][kRC][CP];
     __shared__ float sDelta[NS][kRC][CP], sBeta[NS][kRC][CP], sR[NS][kRC][CP];
     __shared__ float sDc[kRC][CP], sDlk[kRC][CP];   // dc, da
@@ -195,6 +197,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     // matrix-core lane coordinates: row / column tl, k slot lg
     const int wv = __builtin_amdgcn_readfirstlane(tid / 64), tl = lane % 16, lg = lane / 16;
     constexpr int NTC = (N + 15) / 16;    // 16-column tiles
+    constexpr int NWV = kRT / 64;         // waves
     constexpr int KM = DK >= 32 ? 8 : 4;  // k values per lane: 32- or 16-deep products
     const int H = f.H, T = f.T, Dv = f.Dv;
     // Workgroups go to the eight XCDs (each with its own L2) round-robin by
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     const size_t sbase = ((size_t)b * H + h) * J * DK * Dv;
 
     // E = dL/dW_T (or 0), [i][col]
-    for (int e = tid; e < DK * N; e += kThreads) {
+    for (int e = tid; e < DK * N; e += kRT) {
         const int i = e / N, col = e % N, j = col / DB, dd = col % DB;
         sE[i][col] = a.grad_state ? a.grad_state[sbase + ((size_t)j * DK + i) * Dv + d0 + dd] : 0.0f;
     }
@@ -231,12 +234,12 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
 
     // Each chunk's HBM inputs are fetched into registers while a later chunk
     // computes: K and Q rows as float4, and per (token, output dim) the J
-    // errors and logits and dL/do.  The staging threads (F0 .. kThreads - 1)
+    // errors and logits and dL/do.  The staging threads (F0 .. kRT - 1)
     // load them and later stage them.  Every such thread loads every item it
     // owns, from a clamped row (the chunk's last token, the last item), with the
     // input dtype fixed at compile time: no load sits behind a branch (a load
     // there is waited for at the join); staging zeroes what lies past the end.
-    constexpr int F0 = 64, FT = kThreads - F0;
+    constexpr int F0 = 64, FT = kRT - F0;
     constexpr int NKQ = (kRC * (DK / 4) + FT - 1) / FT;
     constexpr int NSC = (kRC * DB + FT - 1) / FT;
     uint4 pk[NKQ] = {}, pq[NKQ] = {};   // (bf16: halves x and y)
@@ -451,7 +454,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     };
     // Gram products of the chunk in slot sl: wave 2 K K^T, wave 3 K Q^T
     auto gram = [&](int sl) {
-        if (wv >= 2) {
+        if (wv == 2 || wv == 3) {
             // D[row][col] = sum_i A[row][i] K[col][i], A = K (D[t][s]) or Q
             // (D[s][t] = k_t . q_s); lane: row / col tl, k slot lg
             const float (*A)[KP] = wv == 2 ? sK[sl] : sQ[sl];
@@ -464,12 +467,16 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
                 if (wv == 2) sGkk[4 * lg + r][tl] = acc[r];
                 else sGkqT[4 * lg + r][tl] = acc[r];
             }
+            // lane (tl, lg) holds rows 4 lg .. + 3 of column tl
+            const int nx = tl + 1;
+            const float lo = nx & 1 ? acc[1] : acc[0], hi = nx & 1 ? acc[3] : acc[2];
+            if (wv == 2 && nx >> 2 == lg) sGsub[nx] = nx & 2 ? hi : lo;
         }
     };
     // base_t = k_t . E + sum_{s>=t} (k_t . q_s) dy_s for the chunk in slot sl: a
     // 16-column tile per wave
     auto base = [&](int sl) {
-        for (int ct = wv; ct < NTC; ct += kThreads / 64) {
+        for (int ct = wv; ct < NTC; ct += kRT / 64) {
             const int col = 16 * ct + tl;
             const bool cv = col < N;
             floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -503,66 +510,74 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     // (one component: ddelta = beta dc), so that the dependent chain from one
     // token's dc to the next is a product, the J-lane sum and two fused
     // multiply-adds.
+    // The wave is bound by its instruction count: a token's dpred reaches the next
+    // token's dc by one multiply-add and the earlier tokens as 4x4x1 fp32 products
+    // (lane = column, four tokens per instruction, all 16 blocks taking the same
+    // four values of K K^T), one batch a token.
     auto tokens = [&](int sl) {
-        // dfr[u] starts at base_u and collects sum_{s>u} (k_u . k_s) dpred_s: dc_u
-        float dfr[kRC], vd[kRC], vbe[kRC], vr[kRC];
+        // D starts at base and collects sum_{s>u} (k_u . k_s) dpred_s: dc_u, four
+        // tokens to a register group
+        floatx4 D[kRC / 4];
+        float vd[kRC], vbe[kRC], vr[kRC], gsub[kRC], g4[kRC / 4];
         const int scw = sact ? scol : N;
 #pragma unroll
-        for (int u = 0; u < kRC; ++u) {
-            dfr[u] = sact ? sBase[u][scol] : 0.0f;
+        for (int u = kRC - 1; u >= 0; --u) {
+            D[u / 4][u % 4] = sact ? sBase[u][scol] : 0.0f;
             vd[u] = sact ? sDelta[sl][u][scol] : 0.0f;
             vbe[u] = sact ? sBeta[sl][u][scol] : 0.0f;
             vr[u] = sact ? sR[sl][u][scol] : 0.0f;
         }
-        // rows of K K^T (= columns), the part u < t: row t - 1 is read while
-        // token t runs, a token ahead of its use
-        float grow[2][kRC];
 #pragma unroll
-        for (int u4 = 0; u4 < kRC / 4; ++u4) {
-            const float4 x = *reinterpret_cast<const float4 *>(&sGkk[kRC - 1][4 * u4]);
-            float *g = grow[(kRC - 1) & 1];
-            g[4 * u4] = x.x, g[4 * u4 + 1] = x.y, g[4 * u4 + 2] = x.z, g[4 * u4 + 3] = x.w;
+        for (int m = 0; m < kRC / 4; ++m) {
+            const float4 x = *reinterpret_cast<const float4 *>(&sGsub[4 * m]);
+            gsub[4 * m] = x.x, gsub[4 * m + 1] = x.y, gsub[4 * m + 2] = x.z, gsub[4 * m + 3] = x.w;
+            g4[m] = sGkk[lane / 4][4 * m + lane % 4];   // block s: tokens 4 m .. + 3
         }
-#pragma unroll
-        for (int t = kRC - 1; t >= 0; --t) {
-#pragma unroll
-            for (int u4 = 0; u4 < (t + 2) / 4; ++u4) {   // row t - 1
-                const float4 x = *reinterpret_cast<const float4 *>(&sGkk[t - 1][4 * u4]);
-                float *g = grow[(t - 1) & 1];
-                g[4 * u4] = x.x, g[4 * u4 + 1] = x.y, g[4 * u4 + 2] = x.z, g[4 * u4 + 3] = x.w;
-            }
-            // (the scheduler would sink these loads to their use: no LDS read may
-            // cross here; arithmetic and LDS writes may)
-            __builtin_amdgcn_sched_barrier(0x207);
-            const float dc = dfr[t];
+        float dc = D[kRC / 4 - 1][3], pprev = 0.0f;
+        auto token = [&](auto tag) {
+            constexpr int t = decltype(tag)::value;
             const float dl = vd[t], br = vbe[t] * vr[t], r = vr[t];
-            float da = 0.0f, ddelta = br * dc;
+            float da = 0.0f, ddelta = br * dc, c = 0.0f, g = 0.0f, cdc = 0.0f;
             if constexpr (J > 1) {
-                const float c = br * dl, g = fmaf(-c, dl, br);   // beta r (1 - delta^2)
-                const float cdc = c * dc;
+                c = br * dl, g = fmaf(-c, dl, br);   // beta r (1 - delta^2)
+                cdc = c * dc;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (t + 1 < kRC) {
+                // dpred of token t + 1 to the tokens before t, the next one's group first
+                constexpr int S = t + 1;
+#pragma unroll
+                for (int m = (S + 2) / 4 - 1; m >= 0; --m)
+                    D[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(g4[m], pprev, D[m], 4, S, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (J > 1) {
                 const float sdr = group_sum<JP>(cdc);
                 da = fmaf(-r, sdr, cdc);
                 ddelta = fmaf(r * dl, sdr, g * dc);
             }
             const float dpred = -ddelta;
-            // (the next token's dc first: it is on the dependent chain)
-#pragma unroll
-            for (int u = t - 1; u >= 0; --u) dfr[u] = fmaf(grow[t & 1][u], dpred, dfr[u]);
             // every lane stores to LDS (idle lanes to a padding column), so that
             // no branch hides from the compiler how many LDS operations are in
-            // flight when the next row of K K^T is waited for
+            // flight
             sP[sl][t][scw] = dpred;
             sDc[t][scw] = dc;
             sDlk[t][scw] = da;
-        }
+            if constexpr (t > 0) dc = fmaf(gsub[t], dpred, D[(t > 0 ? t - 1 : 0) / 4][(t > 0 ? t - 1 : 0) % 4]);
+            pprev = dpred;
+        };
+        token(ITag<15>{}), token(ITag<14>{}), token(ITag<13>{}), token(ITag<12>{});
+        token(ITag<11>{}), token(ITag<10>{}), token(ITag<9>{}), token(ITag<8>{});
+        token(ITag<7>{}), token(ITag<6>{}), token(ITag<5>{}), token(ITag<4>{});
+        token(ITag<3>{}), token(ITag<2>{}), token(ITag<1>{}), token(ITag<0>{});
     };
     // E += Q^T Y + K^T P for the chunk in slot sl (E then holds the gradient
     // from the tokens after the previous chunk), in 16 x 16 tiles of E
     auto update_e = [&](int sl) {
-        // tiles wv, wv + 4, ..., two at a time with every LDS read of both
+        // tiles wv, wv + NWV, ..., two at a time with every LDS read of both
         // issued before their products (a clamped duplicate past the end
         // is computed and not stored)
-        constexpr int NTL = (DK / 16) * NTC, NU = (NTL + 3) / 4;
+        constexpr int NTL = (DK / 16) * NTC, NU = (NTL + NWV - 1) / NWV;
 #pragma unroll
         for (int u0 = 0; u0 < NU; u0 += 2) {
             constexpr int NP2 = NU > 1 ? 2 : 1;
@@ -571,7 +586,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
             KOp<4, PE> yb[NP2], pb[NP2];
 #pragma unroll
             for (int x = 0; x < NP2; ++x) {
-                const int tile = min(wv + 4 * (u0 + x), NTL - 1);
+                const int tile = min(wv + NWV * (u0 + x), NTL - 1);
                 const int ti = tile / NTC, col = 16 * (tile % NTC) + tl;
                 const bool cv = col < N;
                 const int cc = cv ? col : 0;
@@ -596,7 +611,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
             }
 #pragma unroll
             for (int x = 0; x < NP2; ++x) {
-                const int tile = wv + 4 * (u0 + x);
+                const int tile = wv + NWV * (u0 + x);
                 const int ti = tile / NTC, col = 16 * (tile % NTC) + tl;
                 if (u0 + x < NU && tile < NTL && col < N) {
 #pragma unroll
@@ -633,11 +648,11 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
         }
     };
     constexpr ITag<64> kF1{};               // the staging threads
-    constexpr ITag<kThreads - 64> kN1{};
+    constexpr ITag<kRT - 64> kN1{};
     constexpr ITag<0> kF0{};                // every thread
-    constexpr ITag<kThreads> kN0{};
-    constexpr ITag<128> kF2{};              // waves 2 and 3
-    constexpr ITag<kThreads - 128> kN2{};
+    constexpr ITag<kRT> kN0{};
+    constexpr ITag<128> kF2{};              // waves 2 and up
+    constexpr ITag<kRT - 128> kN2{};
 
 
     if (NCH > 0) {
@@ -673,7 +688,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
             if constexpr (NTC > 2) outputs(n, sl, kF0, kN0);
             block_sync_lds();   // C: E now from the tokens after chunk n - 1
             if (n > 0) base(sl ^ 1);   // waves 0 .. NTC - 1
-            // (with two column tiles, waves 2 and 3 store the outputs meanwhile)
+            // (with two column tiles, waves 2 and up store the outputs meanwhile)
             if constexpr (NTC <= 2) {
                 if (wv >= 2) outputs(n, sl, kF2, kN2);
             }
@@ -684,7 +699,7 @@ __global__ __launch_bounds__(kThreads) void reverse_chunk_kernel(BackwardArgs a)
     }
     block_sync_lds();
     if (a.dstate) {
-        for (int e = tid; e < J * DK * DB; e += kThreads) {
+        for (int e = tid; e < J * DK * DB; e += kRT) {
             const int j = e / (DK * DB), i = (e / DB) % DK, dd = e % DB;
             a.dstate[sbase + ((size_t)j * DK + i) * Dv + d0 + dd] = sE[i][j * DB + dd];
         }
@@ -1064,10 +1079,10 @@ hipError_t launch_reverse(const BackwardArgs &a, hipStream_t stream) {
     } else {
         const dim3 grid((unsigned)((a.f.Dv / DB) * a.f.H * a.f.B));
         if (a.f.in_bf16)
-            hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, true>), grid, dim3(kThreads), 0,
+            hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, true>), grid, dim3(kRT), 0,
                                stream, a);
         else
-            hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, false>), grid, dim3(kThreads), 0,
+            hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, false>), grid, dim3(kRT), 0,
                                stream, a);
         return hipGetLastError();
     }
