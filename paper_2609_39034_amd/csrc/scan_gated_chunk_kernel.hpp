@@ -513,7 +513,27 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         };
         // retrieval of chunk m: Y = Y0 + tril(QG) C, times pi^q, to py
         auto retrieve = [&](int m) {
-            const floatx4 y = mm<NP>(QGr, coeffs(m), Y0r);   // D[t = 4 lg + r][col]
+            float4 c4 = *reinterpret_cast<const float4 *>(&sm.c[m & 1][tcol][4 * lg]);
+            if (!tvalid) c4 = make_float4(0.f, 0.f, 0.f, 0.f);
+            // A coefficient that is not finite (an input that is not) would reach the
+            // tokens before its own too, as 0 times it: such ones are taken out of the
+            // product, and the column's tokens from the first on set to NaN.
+            const bool odd = __builtin_amdgcn_ballot_w64(!(fabsf((c4.x + c4.y) + (c4.z + c4.w)) < INFINITY)) != 0;
+            int first = kGC;
+            if (odd) {
+                float *const c = &c4.x;
+#pragma unroll
+                for (int r = 3; r >= 0; --r)
+                    if (!(fabsf(c[r]) < INFINITY)) c[r] = 0.f, first = 4 * lg + r;
+                first = min(first, __shfl_xor(first, 16));
+                first = min(first, __shfl_xor(first, 32));
+            }
+            floatx4 y = mm<NP>(QGr, split4<NP>(c4.x, c4.y, c4.z, c4.w), Y0r);   // D[t = 4 lg + r][col]
+            if (odd) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (4 * lg + r >= first) y[r] = NAN;
+            }
             if (tvalid) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {

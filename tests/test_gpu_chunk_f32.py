@@ -98,3 +98,21 @@ def test_rerun_with_the_maximum_subtracted(form, at):
 ])
 def test_other_calls_keep_the_token_scan(form, B, H, T, Dk, Dv, J):
     _check(form, B, H, T, Dk, Dv, J, 0.1, 2.0, True, 1570 + J, same=True)
+
+
+# what is not finite at one token leaves the tokens before it as they are, also
+# those of its own chunk, and every other output dim
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("name,value", [("v", np.nan), ("v", np.inf), ("beta_logit", np.nan)])
+def test_not_finite_reaches_later_tokens_only(form, name, value):
+    B, H, T, Dk, Dv, J, at = 1, 2, 45, 32, 16, 4, 23
+    inp = workloads.iid_inputs(B, H, T, Dk, Dv, J, dtype="f32", seed=1590, state_std=0.1)
+    tmp = workloads.temporal_inputs(B, H, T, Dv, J, dtype="f32", seed=1590, prior_state=True)
+    dec = workloads.gated_inputs(B, H, T, Dk, J, dtype="f32", seed=1590, mean=2.0)["decay"]
+    inp[NAMES[2] if name == "v" else NAMES[3]][0, at, 1, ..., 5] = value
+    a, r = _run(form, inp, tmp, dec, "auto"), _run(form, inp, tmp, dec, "recurrent")
+    o, want = a[0], np.isfinite(r[0])
+    assert want[:, :at].all() and want[:, :, 0].all() and not want[0, at:, 1, 5].any()
+    assert np.array_equal(np.isfinite(o), want)
+    assert _rel(o[want], r[0][want]) <= TOL
+    assert np.array_equal(np.isfinite(a[1]), np.isfinite(r[1]))
