@@ -130,14 +130,29 @@ __device__ __forceinline__ S4<P> zero4() {
     return s;
 }
 // a b with both operands split: the products of parts p and r with p + r < P
-// (hi hi + hi lo + lo hi; with three parts six products, dropping about 2^-26)
+// (hi hi + hi lo + lo hi; with three parts six products, dropping about 2^-26).
+// With three parts the small products are summed apart, smallest first, so that
+// acc is rounded twice and not six times.
+template <int P, typename V, typename M>
+__device__ __forceinline__ floatx4 mm_parts(const V (&a)[P], const V (&b)[P], floatx4 acc, M &&mul) {
+    if constexpr (P == 3) {
+        floatx4 lo = mul(a[2], b[0], floatx4{0.f, 0.f, 0.f, 0.f});
+        lo = mul(a[1], b[1], lo);
+        lo = mul(a[0], b[2], lo);
+        lo = mul(a[1], b[0], lo);
+        lo = mul(a[0], b[1], lo);
+        return mul(a[0], b[0], acc) + lo;
+    } else {
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int r = 0; r < P - p; ++r) acc = mul(a[p], b[r], acc);
+        return acc;
+    }
+}
 template <int P>
 __device__ __forceinline__ floatx4 mm(const S4<P> &a, const S4<P> &b, floatx4 acc) {
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int r = 0; r < P - p; ++r) acc = mfma16(a.x[p], b.x[r], acc);
-    return acc;
+    return mm_parts<P>(a.x, b.x, acc, [](short4v x, short4v y, floatx4 c) { return mfma16(x, y, c); });
 }
 // The same over two 16-wide k tiles at once (a0 b0 + a1 b1), on the 32-deep
 // instruction: a lane's eight k elements are its four of tile 0, then its four
@@ -155,12 +170,9 @@ __device__ __forceinline__ floatx4 mmx2(const S4<P> &a0, const S4<P> &a1, const 
     bf16x8 a[P], b[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) a[p] = join8(a0.x[p], a1.x[p]), b[p] = join8(b0.x[p], b1.x[p]);
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int r = 0; r < P - p; ++r)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[p], b[r], acc, 0, 0, 0);
-    return acc;
+    return mm_parts<P>(a, b, acc, [](bf16x8 x, bf16x8 y, floatx4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+    });
 }
 
 template <int V>
