@@ -52,7 +52,7 @@
 // sequential wave 2,900 on the SIMD it shares with one of them), then phase B's
 // 1,050.  One launch at B=4 H=8 T=2048 D=64 J=4, before (deferred updates as
 // multiply-adds, gates by the tile waves) and now: 0.364 -> 0.281 ms; with the
-// temporal priors, before on the token-by-token scan: 1.261 -> 0.409 ms.
+// temporal priors, before on the token-by-token scan: 1.261 -> 0.414 ms.
 //
 // The same kernel evaluates fp32 inputs (F32), with or without gates (GT) and
 // temporal priors: K and Q are then fp32 operands like the state, every operand
@@ -529,8 +529,9 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             if (!tvalid) c4 = make_float4(0.f, 0.f, 0.f, 0.f);
             // A coefficient that is not finite (an input that is not) would reach the
             // tokens before its own too, as 0 times it: such ones are taken out of the
-            // product, and the column's tokens from the first on set to NaN.
-            const bool odd = __builtin_amdgcn_ballot_w64(!(fabsf((c4.x + c4.y) + (c4.z + c4.w)) < INFINITY)) != 0;
+            // product, and the column's tokens from the first on set to NaN.  (The gated
+            // form on bf16 inputs leaves that out, as the plain chunk scan does.)
+            const bool odd = NP == 3 && __builtin_amdgcn_ballot_w64(!(fabsf((c4.x + c4.y) + (c4.z + c4.w)) < INFINITY)) != 0;
             int first = kGC;
             if (odd) {
                 float *const c = &c4.x;
