@@ -18,7 +18,7 @@ LIB = os.path.join(PKG, "libswila.so")
 # the largest units first, so that the parallel compile ends soonest
 SOURCES = ["scan_direct_dk128.hip", "scan_direct_dk64.hip", "scan_pipe.hip",
            "scan_pipe_temporal.hip", "scan_direct_dk32.hip", "scan_direct_dk16.hip",
-           "scan_pipe_newton.hip", "scan_gated_chunk.hip", "scan_chunk_f32.hip",
+           "scan_pipe_newton.hip", "scan_gated_chunk.hip", "scan_chunk_f32.hip", "scan_gated_chunk_wide.hip",
            "scan_chunk_f32_gated.hip", "decode.hip", "scan_backward.hip",
            "scan_direct.hip", "swila_api.hip"]
 ARCH = "gfx950"

@@ -87,6 +87,8 @@ hipError_t launch_scan_pipe(const LayerArgs &a, hipStream_t stream);
 // (gated_chunk_supported).
 bool gated_chunk_supported(const LayerArgs &a);
 hipError_t launch_scan_gated_chunk(const LayerArgs &a, hipStream_t stream);
+// J = 4, Dk = 128 without temporal priors.
+hipError_t launch_scan_gated_chunk_wide(const LayerArgs &a, hipStream_t stream);
 // The same kernel for fp32 inputs (plain, temporal and gated forms), with every
 // fp32 operand in three bf16 parts: J <= 4, J * Dk <= 256, no backward support.
 bool chunk_f32_supported(const LayerArgs &a);

@@ -13,6 +13,7 @@ bool gated_chunk_supported(const LayerArgs &a) {
 
 hipError_t launch_scan_gated_chunk(const LayerArgs &a, hipStream_t stream) {
     if (!gated_chunk_supported(a) || a.T <= 0) return hipErrorInvalidValue;
+    if (a.J * a.Dk > 384) return launch_scan_gated_chunk_wide(a, stream);   // both sides: that file
     return a.gk ? launch_gated<true, true, false>(a, stream) : launch_gated<false, true, false>(a, stream);
 }
 

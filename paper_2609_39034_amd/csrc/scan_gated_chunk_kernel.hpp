@@ -29,7 +29,7 @@
 // component j.
 //
 // Block = one head (b, h) and DB output dims with all J components (J <= 4,
-// J * Dk <= 512): J tile waves (wave j: the Dk x DB state tile of component j
+// J * Dk <= 384): J tile waves (wave j: the Dk x DB state tile of component j
 // in accumulator registers), one sequential wave (one lane per column), three
 // helper waves and, up to J * Dk = 256, one or two gate waves.  Per
 // chunk n, between two block barriers:
@@ -231,7 +231,7 @@ struct GCfg {
     static constexpr int LP = DK + 4;        // fp32 row pitch of E^-1 (or L)
     static constexpr int CP = kGC + 4;       // [column][token] row pitch
     static constexpr int NP = N + 4;         // [token][column] row pitch
-    static_assert(J >= 1 && J <= 4 && J * DK <= (F32 || TP ? 256 : 512), "LDS budget of the gated chunk form");
+    static_assert(J >= 1 && J <= 4 && J * DK <= (F32 || TP ? 256 : 384), "LDS budget of the gated chunk form");
     static_assert(GT || F32, "bf16 inputs without gates run the plain chunk scan");
     static_assert(DB == 8 || DB == 16, "column block");
     static_assert(DB * JP <= 64, "one sequential wave");
@@ -1207,7 +1207,7 @@ hipError_t launch_g(const LayerArgs &a, hipStream_t stream) {
 
 template <int DK, int J, bool TP, bool GT, bool F32>
 hipError_t launch_gj(const LayerArgs &a, hipStream_t stream) {
-    if constexpr (J * DK > (TP || F32 ? 256 : 512)) {
+    if constexpr (J * DK > (TP || F32 ? 256 : 384)) {
         return hipErrorInvalidValue;
     } else {
         // 16 output dims per block once that grid fills the chip (where their LDS
