@@ -16,8 +16,9 @@
 // every E^-1 stays below e^{40}.  E^-1 is the running product of 1 + e^{-x}
 // over the chunk's decay logits x (1 / sigmoid), one exponential per element,
 // and E its reciprocal; a chunk whose gates decay further (some E^-1_C above
-// e^{40}) forms its cumulative log gates L instead and the Gram products with
-// the per-pair exponent.  The scaled operands are fp32: each is split into a
+// e^{40}, or a gate closed altogether) keeps its gates a_t instead and takes every
+// factor as the product of the gates between its two tokens
+// (gated_chunk_common.hpp).  The scaled operands are fp32: each is split into a
 // bf16 high part and a bf16 residual, and the hi*hi + hi*lo + lo*hi products
 // are summed (about 2^-16 relative per product, fp32 accumulation).  With the
 // temporal priors (App. B.3), a form that had only the token-by-token scan's fp32
@@ -64,144 +65,23 @@
 #pragma once
 #include <type_traits>
 
-#include "device_common.hpp"
+#include "gated_chunk_common.hpp"
 #include "launch.hpp"
 
 namespace swila {
 namespace {
 
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-constexpr int kGC = 16;              // tokens per chunk
 constexpr int kGH = 3;               // helper waves
 // roles of the ten waves of a block with four tile and two gate waves, four bits
 // each from wave 0 up: tiles 0 - 3, gate 9, helper 5, sequential 4, gate 8,
 // helpers 7 and 6
 constexpr uint64_t kRoles4 = 0x6784593210ull;
-constexpr float kGramEinv = 2.35385266837019985e17f;   // e^40: factorised Gram products while every E^-1 <= this
-// The sequential wave works in scaled units: with s^2 = log2(e) / 2, d = s (v - pred)
-// makes the E-step exponent log2(e) (lk - delta^2 / 2) a single fused multiply-add,
-// -d * d + log2(e) lk, and the coefficient s c = beta r d feeds s pred.
-constexpr float kS = 0.84932180028801904272f;      // sqrt(log2(e) / 2)
-constexpr float kInvS = 1.17741002251547469101f;   // 1 / kS
-constexpr float kS2 = 0.72134752044448170368f;     // kS^2
-constexpr int ceil_div_c(int x, int y) { return (x + y - 1) / y; }
-
-__device__ __forceinline__ floatx4 mfma16(short4v a, short4v b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-
-// Four fp32 values as P bf16 parts each: a high part (round to nearest) and P - 1
-// residuals, converted two at a time.  Two parts are good to about 2^-17 of the
-// value, three to all of its 24 bits.
-template <int P>
-struct S4 {
-    short4v x[P];
-};
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-template <int P>
-__device__ __forceinline__ void split2(float a, float b, uint32_t (&o)[P]) {
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        o[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2v));
-        a -= __uint_as_float(o[p] << 16);
-        b -= __uint_as_float(o[p] & 0xffff0000u);
-    }
-}
-template <int P>
-__device__ __forceinline__ S4<P> split4(float x0, float x1, float x2, float x3) {
-    uint32_t u[P], v[P];
-    split2<P>(x0, x1, u);
-    split2<P>(x2, x3, v);
-    S4<P> s;
-#pragma unroll
-    for (int p = 0; p < P; ++p) s.x[p] = __builtin_bit_cast(short4v, make_uint2(u[p], v[p]));
-    return s;
-}
-template <int P>
-__device__ __forceinline__ S4<P> split4(floatx4 x) { return split4<P>(x[0], x[1], x[2], x[3]); }
-template <int P>
-__device__ __forceinline__ S4<P> zero4() {
-    S4<P> s;
-#pragma unroll
-    for (int p = 0; p < P; ++p) s.x[p] = short4v{0, 0, 0, 0};
-    return s;
-}
-// a b with both operands split: the products of parts p and r with p + r < P
-// (hi hi + hi lo + lo hi; with three parts six products, dropping about 2^-26).
-// With three parts the small products are summed apart, smallest first, so that
-// acc is rounded twice and not six times.
-template <int P, typename V, typename M>
-__device__ __forceinline__ floatx4 mm_parts(const V (&a)[P], const V (&b)[P], floatx4 acc, M &&mul) {
-    if constexpr (P == 3) {
-        floatx4 lo = mul(a[2], b[0], floatx4{0.f, 0.f, 0.f, 0.f});
-        lo = mul(a[1], b[1], lo);
-        lo = mul(a[0], b[2], lo);
-        lo = mul(a[1], b[0], lo);
-        lo = mul(a[0], b[1], lo);
-        return mul(a[0], b[0], acc) + lo;
-    } else {
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-#pragma unroll
-            for (int r = 0; r < P - p; ++r) acc = mul(a[p], b[r], acc);
-        return acc;
-    }
-}
-template <int P>
-__device__ __forceinline__ floatx4 mm(const S4<P> &a, const S4<P> &b, floatx4 acc) {
-    return mm_parts<P>(a.x, b.x, acc, [](short4v x, short4v y, floatx4 c) { return mfma16(x, y, c); });
-}
-// The same over two 16-wide k tiles at once (a0 b0 + a1 b1), on the 32-deep
-// instruction: a lane's eight k elements are its four of tile 0, then its four
-// of tile 1, in both operands.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ bf16x8 join8(short4v x, short4v y) {
-    return __builtin_bit_cast(bf16x8, make_uint4(__builtin_bit_cast(uint2, x).x,
-                                                 __builtin_bit_cast(uint2, x).y,
-                                                 __builtin_bit_cast(uint2, y).x,
-                                                 __builtin_bit_cast(uint2, y).y));
-}
-template <int P>
-__device__ __forceinline__ floatx4 mmx2(const S4<P> &a0, const S4<P> &a1, const S4<P> &b0,
-                                        const S4<P> &b1, floatx4 acc) {
-    bf16x8 a[P], b[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) a[p] = join8(a0.x[p], a1.x[p]), b[p] = join8(b0.x[p], b1.x[p]);
-    return mm_parts<P>(a, b, acc, [](bf16x8 x, bf16x8 y, floatx4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
-    });
-}
-
-template <int V>
-struct ITag {
-    static constexpr int value = V;
-};
-
-__device__ __forceinline__ float bf(float x) { return x; }   // (an fp32 input as it is)
-__device__ __forceinline__ float bf(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// four consecutive inputs of an LDS row
-__device__ __forceinline__ float4 in4(const uint16_t *p) {
-    const uint2 r = *reinterpret_cast<const uint2 *>(p);
-    return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
-                       __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
-}
-__device__ __forceinline__ float4 in4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 // input y of a 16-byte piece (y a compile-time index)
 template <bool F32>
 __device__ __forceinline__ float piece(const uint4 &r, int y) {
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
     return F32 ? __uint_as_float(w[y % 4])
                : __uint_as_float(y % 2 ? w[y / 2 % 4] & 0xffff0000u : w[y / 2 % 4] << 16);
-}
-
-// log sigmoid(x) = min(x, 0) - log(1 + e^{-|x|})
-__device__ __forceinline__ float log_sigmoid(float x) {
-    const float e = __builtin_amdgcn_exp2f(-fabsf(x) * kLog2e);
-    return fminf(x, 0.0f) - __builtin_amdgcn_logf(1.0f + e) * 0.69314718055994531f;
 }
 
 // TP: with the temporal priors (App. B.3); GT: with gates; F32: fp32 inputs.
@@ -228,7 +108,7 @@ struct GCfg {
     static constexpr bool SCALED = !TP && !F32;
     static constexpr float S = SCALED ? kS : 1.0f, IS = SCALED ? kInvS : 1.0f;
     static constexpr int KP = DK + 4;        // bf16 row pitch of the K, Q tiles
-    static constexpr int LP = DK + 4;        // fp32 row pitch of E^-1 (or L)
+    static constexpr int LP = DK + 4;        // fp32 row pitch of E^-1 (or the gates)
     static constexpr int CP = kGC + 4;       // [column][token] row pitch
     static constexpr int NP = N + 4;         // [token][column] row pitch
     static_assert(J >= 1 && J <= 4 && J * DK <= (F32 || TP ? 256 : 384), "LDS budget of the gated chunk form");
@@ -247,7 +127,7 @@ struct GSmem {
     alignas(16) In lq[3][kGC][C::N];   // [token][j * DB + dd]
     // decay logits of the next chunk to take its gates (tile waves' gates)
     alignas(16) uint16_t g[C::HG || !GT ? 1 : kGC][C::HG || !GT ? 8 : J * DK];
-    // E^-1 of chunk m (its cumulative log gates L in a deep chunk), and E_C, in
+    // E^-1 of chunk m (its gates a_t in a deep chunk), and E_C, in
     // slots m % NEI and m % NEC; with gate waves, whether the chunk is deep
     alignas(16) float ei[GT ? C::NEI : 1][GT ? J : 1][GT ? kGC : 1][GT ? C::LP : 4];
     alignas(16) float ec[GT ? C::NEC : 1][GT ? J : 1][GT ? DK : 4];
@@ -271,20 +151,6 @@ struct GSmem {
     float pq[2][kGC][C::NP];                 // pi^q [token][column]
     float py[2][kGC][C::NP];                 // pi^q * retrieval [token][column]
 };
-
-// Block -> (column block, head): the column blocks of a head on one XCD
-// (workgroups go to the eight XCDs round-robin by index, each with its own L2),
-// so that the head's K, Q and gate rows are fetched from HBM once.
-__device__ __forceinline__ void gated_coords(int id, int ndb, int nheads, int &db, int &head) {
-    if (nheads % 8 == 0) {
-        const int k = id / 8;
-        head = id % 8 + 8 * (k / ndb);
-        db = k % ndb;
-    } else {
-        head = id / ndb;
-        db = id % ndb;
-    }
-}
 
 // Each role runs its whole chunk loop in a branch of its own, so that the
 // registers one role keeps across chunks are not held by the others; every
@@ -326,7 +192,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         const int tj = w;
         const bool tvalid = tl < DB;
         const int tcol = tj * DB + (tvalid ? tl : 0);
-        // E^-1 (or L) of chunk m, [token][key index]
+        // E^-1 (in a deep chunk the gates) of chunk m, [token][key index]
         auto ei_of = [&](int m) { return sm.ei[HG ? m % 3 : 0][GT ? tj : 0]; };
         floatx4 W[IT];
         S4<NP> Kp[IT];   // K_m (.) E_m for the next chunk m, A operand (rows t = tl)
@@ -338,7 +204,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         S4<NP> QGr = zero4<NP>(), QGq = zero4<NP>();
         bool deep_n = false, deep_n1 = false;   // chunk n, n+1 past the factorised Gram products
 
-        // E^-1 (or, in a deep chunk, L) and E_C of chunk m for component tj from
+        // E^-1 (in a deep chunk the gates) and E_C of chunk m for component tj from
         // its decay logits (lane: key index lane, or 2 lane and 2 lane + 1 when
         // Dk = 128); returns whether the chunk is deep.
         auto log_gates = [&](int m) {
@@ -370,16 +236,16 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) = make_float2(rcp_fast(c0), rcp_fast(c1));
                 deep = !(c0 <= kGramEinv) || !(c1 <= kGramEinv);
                 if (__any(deep) == 0) return false;
-                // deep chunk: L = the running sum of log sigmoid, in place of E^-1
-                float l0 = 0.0f, l1 = 0.0f;
+                // deep chunk: the gates, in place of E^-1
+                float l0 = 1.0f, l1 = 1.0f;
 #pragma unroll
                 for (int t = 0; t < kGC; ++t) {
-                    l0 += t < nt ? log_sigmoid(__uint_as_float(x[t] << 16)) : 0.0f;
-                    l1 += t < nt ? log_sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 0.0f;
-                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(l0, l1);
+                    const float a0 = t < nt ? sigmoid(__uint_as_float(x[t] << 16)) : 1.0f;
+                    const float a1 = t < nt ? sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 1.0f;
+                    l0 *= a0, l1 *= a1;
+                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(a0, a1);
                 }
-                *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) =
-                    make_float2(__builtin_amdgcn_exp2f(kLog2e * l0), __builtin_amdgcn_exp2f(kLog2e * l1));
+                *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) = make_float2(l0, l1);
                 return true;
             } else {
                 // one key index per lane (lanes past Dk idle)
@@ -404,13 +270,14 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 }
                 if (__any(deep) == 0) return false;
                 if (DK >= 64 || i < DK) {
-                    float l = 0.0f;
+                    float l = 1.0f;
 #pragma unroll
                     for (int t = 0; t < kGC; ++t) {
-                        l += t < nt ? log_sigmoid(x[t]) : 0.0f;
-                        EI[t][i] = l;
+                        const float at = t < nt ? sigmoid(x[t]) : 1.0f;
+                        l *= at;
+                        EI[t][i] = at;
                     }
-                    sm.ec[m % C::NEC][tj][i] = __builtin_amdgcn_exp2f(kLog2e * l);
+                    sm.ec[m % C::NEC][tj][i] = l;
                 }
                 return true;
             }
@@ -422,16 +289,6 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             const float4 x = in4(&X[tl][16 * it + 4 * lg]);
             return GT ? split4<NP>(x.x * f.x, x.y * f.y, x.z * f.z, x.w * f.w)
                       : split4<NP>(x.x, x.y, x.z, x.w);
-        };
-        // per-pair exponent (deep chunk m, L in EI): sum_i X[t][i] K[s][i] e^{L_ti - L_si}
-        auto pair_dot = [&](const In (*X)[C::KP], int m, int t, int s) {
-            float acc = 0.0f;
-            auto *const EI = ei_of(m);
-#pragma unroll 1
-            for (int i = 0; i < DK; ++i)
-                acc = fmaf(bf(X[t][i]) * bf(sm.k[m % 3][s][i]),
-                           __builtin_amdgcn_exp2f(kLog2e * (EI[t][i] - EI[s][i])), acc);
-            return acc;
         };
         // the operands of chunk m: Kp, Qe, G_m (for the sequential wave) and QG_m
         auto gram = [&](int m, bool pair) {
@@ -471,22 +328,12 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 for (int r = 0; r < 4; ++r)
                     if (4 * lg + r > tl) qg[r] = 0.0f;
             } else if constexpr (GT) {
+                deep_grams<DK, NP>(EI, sm.k[s3], sm.q[s3], tl, lg, g, qg);
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
-                    const float4 x = *reinterpret_cast<const float4 *>(&EI[tl][16 * it + 4 * lg]);
-                    const float4 er = make_float4(__builtin_amdgcn_exp2f(kLog2e * x.x),
-                                                  __builtin_amdgcn_exp2f(kLog2e * x.y),
-                                                  __builtin_amdgcn_exp2f(kLog2e * x.z),
-                                                  __builtin_amdgcn_exp2f(kLog2e * x.w));
+                    const float4 er = decay_to(EI, tl, 16 * it + 4 * lg);
                     Kp[it] = row4(sm.k[s3], it, er);
                     Qe[it] = row4(sm.q[s3], it, er);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int t = 4 * lg + r;   // row of G
-                    const int s = 4 * lg + r;   // column of QG
-                    g[r] = t > tl ? pair_dot(sm.k[s3], m, t, tl) : 0.0f;
-                    qg[r] = s <= tl ? pair_dot(sm.q[s3], m, tl, s) : 0.0f;
                 }
             }
             // lane (tl, lg) holds G of tokens 4 lg + r, column s = tl
@@ -556,7 +403,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             }
         };
         // what chunk n needs besides C_n: its Q S and tril(QG) for the retrieval
-        // (from Y0q and QGq) and U_n (EI holds chunk n's E^-1 or L)
+        // (from Y0q and QGq) and U_n (EI holds chunk n's E^-1 or gates)
         auto prepare = [&](int n, bool pair) {
             const int s3 = n % 3;
             auto *const EI = ei_of(n);
@@ -580,13 +427,10 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
                     const int i = 16 * it + tl;
-                    const float lc = EI[kGC - 1][i];
-                    float u[4];
+                    float u[4], f[4];
+                    decay_after(EI, lg, i, f);
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const int s = 4 * lg + m;
-                        u[m] = bf(sm.k[s3][s][i]) * __builtin_amdgcn_exp2f(kLog2e * (lc - EI[s][i]));
-                    }
+                    for (int m = 0; m < 4; ++m) u[m] = bf(sm.k[s3][4 * lg + m][i]) * f[m];
                     U[it] = split4<NP>(u[0], u[1], u[2], u[3]);
                 }
             }
@@ -893,15 +737,14 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             const uint64_t cm = CL == 64 ? ~0ull : ((1ull << (CL % 64)) - 1) << (lane / CL * CL);
             const bool deep = (all & cm) != 0;
             if (all != 0 && deep) {
-                // deep chunk: L = the running sum of log sigmoid, in place of E^-1
-                float l0 = 0.0f, l1 = 0.0f;
+                // deep chunk: the gates, in place of E^-1
+                r0 = r1 = 1.0f;
 #pragma unroll
                 for (int t = 0; t < kGC; ++t) {
-                    l0 += t < nt ? log_sigmoid(lo_of(x[t])) : 0.0f;
-                    l1 += t < nt ? log_sigmoid(hi_of(x[t])) : 0.0f;
-                    f0[t] = l0, f1[t] = l1;
+                    f0[t] = t < nt ? sigmoid(lo_of(x[t])) : 1.0f;
+                    f1[t] = t < nt ? sigmoid(hi_of(x[t])) : 1.0f;
+                    r0 *= f0[t], r1 *= f1[t];
                 }
-                r0 = __builtin_amdgcn_exp2f(kLog2e * l0), r1 = __builtin_amdgcn_exp2f(kLog2e * l1);
             }
             if (act) {
 #pragma unroll

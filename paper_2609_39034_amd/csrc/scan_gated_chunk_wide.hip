@@ -24,8 +24,9 @@
 // every E^-1 stays below e^{40}.  E^-1 is the running product of 1 + e^{-x}
 // over the chunk's decay logits x (1 / sigmoid), one exponential per element,
 // and E its reciprocal; a chunk whose gates decay further (some E^-1_C above
-// e^{40}) forms its cumulative log gates L instead and the Gram products with
-// the per-pair exponent.  The scaled operands are fp32: each is split into a
+// e^{40}, or a gate closed altogether) keeps its gates a_t instead and takes every
+// factor as the product of the gates between its two tokens
+// (gated_chunk_common.hpp).  The scaled operands are fp32: each is split into a
 // bf16 high part and a bf16 residual, and the hi*hi + hi*lo + lo*hi products
 // are summed (about 2^-16 relative per product, fp32 accumulation).  A
 // component's gates differ from the others', so each component has its own
@@ -48,91 +49,13 @@
 //              P_{n+1} = (K_{n+1} (.) E_{n+1}) S_{n+1} for the next recurrence;
 //            sequential wave: beta, key-prior logits and v of chunk n+1;
 //            helper waves: the decay logits of chunk n+2, the loads of n+3.
-#include "device_common.hpp"
+#include "gated_chunk_common.hpp"
 #include "launch.hpp"
 
 namespace swila {
 namespace {
 
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-constexpr int kGC = 16;              // tokens per chunk
 constexpr int kGH = 3;               // helper waves
-constexpr float kGramEinv = 2.35385266837019985e17f;   // e^40: factorised Gram products while every E^-1 <= this
-// The sequential wave works in scaled units: with s^2 = log2(e) / 2, d = s (v - pred)
-// makes the E-step exponent log2(e) (lk - delta^2 / 2) a single fused multiply-add,
-// -d * d + log2(e) lk, and the coefficient s c = beta r d feeds s pred.
-constexpr float kS = 0.84932180028801904272f;      // sqrt(log2(e) / 2)
-constexpr float kInvS = 1.17741002251547469101f;   // 1 / kS
-constexpr int ceil_div_c(int x, int y) { return (x + y - 1) / y; }
-
-__device__ __forceinline__ floatx4 mfma16(short4v a, short4v b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-
-// Four fp32 values as bf16 high parts (round to nearest) and bf16 residuals,
-// converted two at a time.
-struct S4 {
-    short4v hi, lo;
-};
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split2(float a, float b, uint32_t &hi, uint32_t &lo) {
-    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2v));
-    const float ah = __uint_as_float(hi << 16), bh = __uint_as_float(hi & 0xffff0000u);
-    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a - ah, b - bh}, bf16x2v));
-}
-__device__ __forceinline__ S4 split4(float x0, float x1, float x2, float x3) {
-    uint32_t h0, l0, h1, l1;
-    split2(x0, x1, h0, l0);
-    split2(x2, x3, h1, l1);
-    S4 s;
-    s.hi = __builtin_bit_cast(short4v, make_uint2(h0, h1));
-    s.lo = __builtin_bit_cast(short4v, make_uint2(l0, l1));
-    return s;
-}
-__device__ __forceinline__ S4 split4(floatx4 x) { return split4(x[0], x[1], x[2], x[3]); }
-__device__ __forceinline__ S4 zero4() {
-    S4 s;
-    s.hi = short4v{0, 0, 0, 0};
-    s.lo = short4v{0, 0, 0, 0};
-    return s;
-}
-// a b with both operands split: hi hi + hi lo + lo hi
-__device__ __forceinline__ floatx4 mm3(const S4 &a, const S4 &b, floatx4 acc) {
-    acc = mfma16(a.hi, b.hi, acc);
-    acc = mfma16(a.hi, b.lo, acc);
-    acc = mfma16(a.lo, b.hi, acc);
-    return acc;
-}
-// The same over two 16-wide k tiles at once (a0 b0 + a1 b1), on the 32-deep
-// instruction: a lane's eight k elements are its four of tile 0, then its four
-// of tile 1, in both operands.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ bf16x8 join8(short4v x, short4v y) {
-    return __builtin_bit_cast(bf16x8, make_uint4(__builtin_bit_cast(uint2, x).x,
-                                                 __builtin_bit_cast(uint2, x).y,
-                                                 __builtin_bit_cast(uint2, y).x,
-                                                 __builtin_bit_cast(uint2, y).y));
-}
-__device__ __forceinline__ floatx4 mm3x2(const S4 &a0, const S4 &a1, const S4 &b0, const S4 &b1,
-                                         floatx4 acc) {
-    const bf16x8 ah = join8(a0.hi, a1.hi), al = join8(a0.lo, a1.lo);
-    const bf16x8 bh = join8(b0.hi, b1.hi), bl = join8(b0.lo, b1.lo);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
-    return acc;
-}
-
-__device__ __forceinline__ float bf(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// log sigmoid(x) = min(x, 0) - log(1 + e^{-|x|})
-__device__ __forceinline__ float log_sigmoid(float x) {
-    const float e = __builtin_amdgcn_exp2f(-fabsf(x) * kLog2e);
-    return fminf(x, 0.0f) - __builtin_amdgcn_logf(1.0f + e) * 0.69314718055994531f;
-}
 
 template <int DK, int J, int DB>
 struct GCfg {
@@ -141,7 +64,7 @@ struct GCfg {
     static constexpr int JP = J == 3 ? 4 : J;
     static constexpr int NWAVE = J + 1 + kGH;
     static constexpr int KP = DK + 4;        // bf16 row pitch of the K, Q tiles
-    static constexpr int LP = DK + 4;        // fp32 row pitch of E^-1 (or L)
+    static constexpr int LP = DK + 4;        // fp32 row pitch of E^-1 (or the gates)
     static constexpr int TP = kGC + 4;       // [column][token] row pitch
     static constexpr int NP = N + 4;         // [token][column] row pitch
     static_assert(J >= 1 && J <= 4 && J * DK <= 512, "LDS budget of the gated chunk form");
@@ -157,7 +80,7 @@ struct GSmem {
     alignas(16) uint16_t q[3][kGC][C::KP];
     alignas(16) uint16_t lq[3][kGC][C::N];   // [token][j * DB + dd]
     alignas(16) uint16_t g[kGC][J * DK];     // decay logits of the next chunk to take its gates
-    // E^-1 of chunk m (its cumulative log gates L in a deep chunk), written and
+    // E^-1 of chunk m (its gates a_t in a deep chunk), written and
     // read by tile wave j only; E_C, chunk m in m & 1
     alignas(16) float ei[J][kGC][C::LP];
     alignas(16) float ec[2][J][DK];
@@ -171,20 +94,6 @@ struct GSmem {
     float pq[2][kGC][C::NP];                 // pi^q [token][column]
     float py[2][kGC][C::NP];                 // pi^q * retrieval [token][column]
 };
-
-// Block -> (column block, head): the column blocks of a head on one XCD
-// (workgroups go to the eight XCDs round-robin by index, each with its own L2),
-// so that the head's K, Q and gate rows are fetched from HBM once.
-__device__ __forceinline__ void gated_coords(int id, int ndb, int nheads, int &db, int &head) {
-    if (nheads % 8 == 0) {
-        const int k = id / 8;
-        head = id % 8 + 8 * (k / ndb);
-        db = k % ndb;
-    } else {
-        head = id / ndb;
-        db = id % ndb;
-    }
-}
 
 // Each role runs its whole chunk loop in a branch of its own, so that the
 // registers one role keeps across chunks are not held by the others; every
@@ -214,16 +123,16 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
         const int tcol = tj * DB + (tvalid ? tl : 0);
         float (*const EI)[C::LP] = sm.ei[tj];
         floatx4 W[IT];
-        S4 Kp[IT];   // K_m (.) E_m for the next chunk m, A operand (rows t = tl)
-        S4 Qe[IT];   // Q_m (.) E_m for the next chunk m (rows t = tl)
-        S4 U[IT];    // update operand of chunk n: rows i = 16 it + tl, columns s = 4 lg + m
+        S4<2> Kp[IT];   // K_m (.) E_m for the next chunk m, A operand (rows t = tl)
+        S4<2> Qe[IT];   // Q_m (.) E_m for the next chunk m (rows t = tl)
+        S4<2> U[IT];    // update operand of chunk n: rows i = 16 it + tl, columns s = 4 lg + m
         // Q S and tril(QG) (A operand) of the chunk whose retrieval is pending
         // (r), and of the chunk after it (q)
         floatx4 Y0r = floatx4{0.f, 0.f, 0.f, 0.f}, Y0q = floatx4{0.f, 0.f, 0.f, 0.f};
-        S4 QGr = zero4(), QGq = zero4();
+        S4<2> QGr = zero4<2>(), QGq = zero4<2>();
         bool deep_n = false, deep_n1 = false;   // chunk n, n+1 past the factorised Gram products
 
-        // E^-1 (or, in a deep chunk, L) and E_C of chunk m for component tj from
+        // E^-1 (in a deep chunk the gates) and E_C of chunk m for component tj from
         // its decay logits (lane: key index lane, or 2 lane and 2 lane + 1 when
         // Dk = 128); returns whether the chunk is deep.
         auto log_gates = [&](int m) {
@@ -249,16 +158,16 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                 *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) = make_float2(rcp_fast(c0), rcp_fast(c1));
                 deep = !(c0 <= kGramEinv) || !(c1 <= kGramEinv);
                 if (__any(deep) == 0) return false;
-                // deep chunk: L = the running sum of log sigmoid, in place of E^-1
-                float l0 = 0.0f, l1 = 0.0f;
+                // deep chunk: the gates, in place of E^-1
+                float l0 = 1.0f, l1 = 1.0f;
 #pragma unroll
                 for (int t = 0; t < kGC; ++t) {
-                    l0 += t < nt ? log_sigmoid(__uint_as_float(x[t] << 16)) : 0.0f;
-                    l1 += t < nt ? log_sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 0.0f;
-                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(l0, l1);
+                    const float a0 = t < nt ? sigmoid(__uint_as_float(x[t] << 16)) : 1.0f;
+                    const float a1 = t < nt ? sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 1.0f;
+                    l0 *= a0, l1 *= a1;
+                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(a0, a1);
                 }
-                *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) =
-                    make_float2(__builtin_amdgcn_exp2f(kLog2e * l0), __builtin_amdgcn_exp2f(kLog2e * l1));
+                *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) = make_float2(l0, l1);
                 return true;
             } else {
                 // one key index per lane (lanes past Dk idle)
@@ -283,13 +192,14 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                 }
                 if (__any(deep) == 0) return false;
                 if (DK >= 64 || i < DK) {
-                    float l = 0.0f;
+                    float l = 1.0f;
 #pragma unroll
                     for (int t = 0; t < kGC; ++t) {
-                        l += t < nt ? log_sigmoid(x[t]) : 0.0f;
-                        EI[t][i] = l;
+                        const float at = t < nt ? sigmoid(x[t]) : 1.0f;
+                        l *= at;
+                        EI[t][i] = at;
                     }
-                    sm.ec[m & 1][tj][i] = __builtin_amdgcn_exp2f(kLog2e * l);
+                    sm.ec[m & 1][tj][i] = l;
                 }
                 return true;
             }
@@ -298,19 +208,10 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
         // four bf16 of row tl of X, key indices 16 it + 4 lg .. + 3, times f
         auto row4 = [&](const uint16_t (*X)[C::KP], int it, float4 f) {
             const uint2 raw = *reinterpret_cast<const uint2 *>(&X[tl][16 * it + 4 * lg]);
-            return split4(__uint_as_float(raw.x << 16) * f.x,
+            return split4<2>(__uint_as_float(raw.x << 16) * f.x,
                           __uint_as_float(raw.x & 0xffff0000u) * f.y,
                           __uint_as_float(raw.y << 16) * f.z,
                           __uint_as_float(raw.y & 0xffff0000u) * f.w);
-        };
-        // per-pair exponent (deep chunk m, L in EI): sum_i X[t][i] K[s][i] e^{L_ti - L_si}
-        auto pair_dot = [&](const uint16_t (*X)[C::KP], int m, int t, int s) {
-            float acc = 0.0f;
-#pragma unroll 1
-            for (int i = 0; i < DK; ++i)
-                acc = fmaf(bf(X[t][i]) * bf(sm.k[m % 3][s][i]),
-                           __builtin_amdgcn_exp2f(kLog2e * (EI[t][i] - EI[s][i])), acc);
-            return acc;
         };
         // the operands of chunk m: Kp, Qe, G_m (for the sequential wave) and QG_m
         auto gram = [&](int m, bool pair) {
@@ -327,15 +228,15 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                     return row4(sm.k[s3], it, x);
                 };
                 if constexpr (IT == 1) {
-                    const S4 kinv = operands(0);
-                    g = mm3(Kp[0], kinv, g);      // D[t = 4 lg + r][s = tl] = G_ts
-                    qg = mm3(kinv, Qe[0], qg);    // D[s = 4 lg + r][t = tl] = QG_ts
+                    const S4<2> kinv = operands(0);
+                    g = mm<2>(Kp[0], kinv, g);      // D[t = 4 lg + r][s = tl] = G_ts
+                    qg = mm<2>(kinv, Qe[0], qg);    // D[s = 4 lg + r][t = tl] = QG_ts
                 } else {
 #pragma unroll
                     for (int it = 0; it < IT; it += 2) {
-                        const S4 k0 = operands(it), k1 = operands(it + 1);
-                        g = mm3x2(Kp[it], Kp[it + 1], k0, k1, g);
-                        qg = mm3x2(k0, k1, Qe[it], Qe[it + 1], qg);
+                        const S4<2> k0 = operands(it), k1 = operands(it + 1);
+                        g = mmx2<2>(Kp[it], Kp[it + 1], k0, k1, g);
+                        qg = mmx2<2>(k0, k1, Qe[it], Qe[it + 1], qg);
                     }
                 }
                 // lane (tl, lg) holds QG[t = tl][s = 4 lg + r]: the A operand of the retrieval
@@ -343,42 +244,32 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                 for (int r = 0; r < 4; ++r)
                     if (4 * lg + r > tl) qg[r] = 0.0f;
             } else {
+                deep_grams<DK, 2>(EI, sm.k[s3], sm.q[s3], tl, lg, g, qg);
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
-                    const float4 x = *reinterpret_cast<const float4 *>(&EI[tl][16 * it + 4 * lg]);
-                    const float4 er = make_float4(__builtin_amdgcn_exp2f(kLog2e * x.x),
-                                                  __builtin_amdgcn_exp2f(kLog2e * x.y),
-                                                  __builtin_amdgcn_exp2f(kLog2e * x.z),
-                                                  __builtin_amdgcn_exp2f(kLog2e * x.w));
+                    const float4 er = decay_to(EI, tl, 16 * it + 4 * lg);
                     Kp[it] = row4(sm.k[s3], it, er);
                     Qe[it] = row4(sm.q[s3], it, er);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int t = 4 * lg + r;   // row of G
-                    const int s = 4 * lg + r;   // column of QG
-                    g[r] = t > tl ? pair_dot(sm.k[s3], m, t, tl) : 0.0f;
-                    qg[r] = s <= tl ? pair_dot(sm.q[s3], m, tl, s) : 0.0f;
                 }
             }
             *reinterpret_cast<float4 *>(&sm.gt[m & 1][tj][tl][4 * lg]) =
                 make_float4(g[0], g[1], g[2], g[3]);
-            QGq = split4(qg);
+            QGq = split4<2>(qg);
         };
         // for the next chunk, from its start state S: the predictions P = Kp S
         // for the sequential wave, in its units, and Q S (Y0q)
         auto predict = [&]() {
             floatx4 pacc = floatx4{0.f, 0.f, 0.f, 0.f}, y0 = floatx4{0.f, 0.f, 0.f, 0.f};
             if constexpr (IT == 1) {
-                const S4 ws = split4(W[0]);
-                pacc = mm3(Kp[0], ws, pacc);   // D[t][col]
-                y0 = mm3(Qe[0], ws, y0);
+                const S4<2> ws = split4<2>(W[0]);
+                pacc = mm<2>(Kp[0], ws, pacc);   // D[t][col]
+                y0 = mm<2>(Qe[0], ws, y0);
             } else {
 #pragma unroll
                 for (int it = 0; it < IT; it += 2) {
-                    const S4 w0 = split4(W[it]), w1 = split4(W[it + 1]);
-                    pacc = mm3x2(Kp[it], Kp[it + 1], w0, w1, pacc);
-                    y0 = mm3x2(Qe[it], Qe[it + 1], w0, w1, y0);
+                    const S4<2> w0 = split4<2>(W[it]), w1 = split4<2>(W[it + 1]);
+                    pacc = mmx2<2>(Kp[it], Kp[it + 1], w0, w1, pacc);
+                    y0 = mmx2<2>(Qe[it], Qe[it + 1], w0, w1, y0);
                 }
             }
             if (tvalid)
@@ -389,11 +280,11 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
         // C of chunk m as the B operand: rows s = 4 lg .. + 3, column tl
         auto coeffs = [&](int m) {
             const float4 c4 = *reinterpret_cast<const float4 *>(&sm.c[m & 1][tcol][4 * lg]);
-            return tvalid ? split4(c4.x, c4.y, c4.z, c4.w) : zero4();
+            return tvalid ? split4<2>(c4.x, c4.y, c4.z, c4.w) : zero4<2>();
         };
         // retrieval of chunk m: Y = Y0 + tril(QG) C, times pi^q, to py
         auto retrieve = [&](int m) {
-            const floatx4 y = mm3(QGr, coeffs(m), Y0r);   // D[t = 4 lg + r][col]
+            const floatx4 y = mm<2>(QGr, coeffs(m), Y0r);   // D[t = 4 lg + r][col]
             if (tvalid) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -403,7 +294,7 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
             }
         };
         // what chunk n needs besides C_n: its Q S and tril(QG) for the retrieval
-        // (from Y0q and QGq) and U_n (EI holds chunk n's E^-1 or L)
+        // (from Y0q and QGq) and U_n (EI holds chunk n's E^-1 or gates)
         auto prepare = [&](int n, bool pair) {
             const int s3 = n % 3;
             Y0r = Y0q;
@@ -420,20 +311,17 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                         const int s = 4 * lg + m;
                         u[m] = bf(sm.k[s3][s][i]) * (ecv * EI[s][i]);
                     }
-                    U[it] = split4(u[0], u[1], u[2], u[3]);
+                    U[it] = split4<2>(u[0], u[1], u[2], u[3]);
                 }
             } else {
 #pragma unroll
                 for (int it = 0; it < IT; ++it) {
                     const int i = 16 * it + tl;
-                    const float lc = EI[kGC - 1][i];
-                    float u[4];
+                    float u[4], f[4];
+                    decay_after(EI, lg, i, f);
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const int s = 4 * lg + m;
-                        u[m] = bf(sm.k[s3][s][i]) * __builtin_amdgcn_exp2f(kLog2e * (lc - EI[s][i]));
-                    }
-                    U[it] = split4(u[0], u[1], u[2], u[3]);
+                    for (int m = 0; m < 4; ++m) u[m] = bf(sm.k[s3][4 * lg + m][i]) * f[m];
+                    U[it] = split4<2>(u[0], u[1], u[2], u[3]);
                 }
             }
         };
@@ -463,7 +351,7 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
             }
             block_sync_lds();   // e(n)
             // ---- phase B: S_{n+1} = E_C (.) S_n + U_n^T C_n, then P_{n+1}, Q_{n+1} S_{n+1}
-            const S4 cb = coeffs(n);
+            const S4<2> cb = coeffs(n);
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
                 const float4 e4 = *reinterpret_cast<const float4 *>(&sm.ec[n & 1][tj][16 * it + 4 * lg]);
@@ -471,7 +359,7 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                 W[it][1] *= e4.y;
                 W[it][2] *= e4.z;
                 W[it][3] *= e4.w;
-                W[it] = mm3(U[it], cb, W[it]);
+                W[it] = mm<2>(U[it], cb, W[it]);
             }
             if (n + 1 < NCH) predict();
             deep_n = deep_n1;
