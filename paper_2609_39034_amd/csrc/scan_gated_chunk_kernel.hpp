@@ -23,8 +23,9 @@
 // are summed (about 2^-16 relative per product, fp32 accumulation).  With the
 // temporal priors (App. B.3), a form that had only the token-by-token scan's fp32
 // arithmetic before, each is split into three parts and six products are summed,
-// which keeps all 24 bits: the state's error against fp64 is 2e-7 to 3.5e-7 over
-// lengths of 17 to 4096 (token scan 1.5e-7).  A
+// which keeps all 24 bits, and E^-1 is formed in 64 bits: the state's error against fp64
+// is 1.3e-7 to 1.5e-7 over lengths of 17 to 4096, that of o 1.1e-7 (token scan 1.4e-7
+// to 1.5e-7, 1.2e-7).  A
 // component's gates differ from the others', so each component has its own
 // Gram matrices and scaled operands: tile wave j holds the state columns of
 // component j.
@@ -72,10 +73,23 @@ namespace swila {
 namespace {
 
 constexpr int kGH = 3;               // helper waves
-// roles of the ten waves of a block with four tile and two gate waves, four bits
-// each from wave 0 up: tiles 0 - 3, gate 9, helper 5, sequential 4, gate 8,
-// helpers 7 and 6
-constexpr uint64_t kRoles4 = 0x6784593210ull;
+// Roles of a block's waves, four bits each from wave 0 up (0: wave x has role x).
+// Wave x runs on SIMD x mod 4, and its older waves go first.  With nine or ten
+// waves some SIMDs have three: the sequential wave takes one that has two and no
+// gate wave, and the gate waves go before the helpers; with six or seven it has one
+// to itself.  Against roles in order, B=4 H=8 T=512 Dv=64: four tile and one gate wave
+// (Dk=32, bf16 gated) 75.9 -> 61.9 us, three and two (Dk=64) 70.7 -> 67.5, two and one
+// (Dk=32) 60.3 -> 53.4.  Eight waves stay in order (J = 3 with one gate wave and J = 2
+// with two: the other orders tried were 3 to 12% slower).
+template <int J, int NG>
+constexpr uint64_t wave_roles() {
+    return J == 4 && NG == 2 ? 0x6784593210ull   // tiles, gate, helper, sequential, gate, helpers
+           : J == 4 && NG == 1 ? 0x765483210ull  // tiles, gate, sequential, helpers
+           : J == 3 && NG == 2 ? 0x654873210ull  // tiles, sequential, gates, helpers
+           : J == 2 && NG == 1 ? 0x5432610ull    // tiles, gate, sequential, helpers
+           : J == 1 && NG == 1 ? 0x432150ull     // tile, gate, sequential, helpers
+                               : 0;
+}
 // input y of a 16-byte piece (y a compile-time index)
 template <bool F32>
 __device__ __forceinline__ float piece(const uint4 &r, int y) {
@@ -171,14 +185,11 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
     __shared__ GSmem<DK, J, DB, TP, GT, F32> sm;
 
     const int tid = threadIdx.x;
-    // Role w of this wave: 0 .. J-1 tile, J sequential, then the helpers, then the
-    // gate waves.  Wave x of a block runs on SIMD x mod 4, and its older waves go
-    // first: with four tile waves the sequential wave takes the third SIMD, which
-    // has no third wave, and the gate waves go before the helpers.
+    // role w of this wave: 0 .. J-1 tile, J sequential, then the helpers, then the
+    // gate waves
     const int wx = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
-    const int w = HG && J == 4 && C::NG == 2
-                      ? (int)((kRoles4 >> (4 * wx)) & 15)
-                      : wx;
+    constexpr uint64_t kRoles = wave_roles<J, C::NG>();
+    const int w = kRoles ? (int)((kRoles >> (4 * wx)) & 15) : wx;
     const int tl = lane % 16, lg = lane / 16;
     const int H = a.H, T = a.T, Dv = a.Dv;
     int db, hh;
@@ -567,14 +578,27 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             // of the chunk's tokens, four to a register group, and a coefficient
             // reaches the next token by one multiply-add and the others as 4x4x1
             // products (a block's A operand is its component's -G), one batch a token.
+            // In the forms that keep all 24 bits D holds -pred and v joins at the
+            // token (one addition more): its 15 updates are rounded at the size of the
+            // prediction and not of v, which was the whole excess of these forms'
+            // error over the token scan's (2-norm of the state against
+            // 64 bits at B=4 H=8 T=256 D=64 J=4, with E^-1 rounded once as well: bf16
+            // gated temporal 2.8e-7 -> 1.5e-7, token scan 1.5e-7; fp32 gated 2.3e-7 ->
+            // 1.2e-7, 1.4e-7; fp32 plain 2.3e-7 -> 1.7e-7, 3.2e-7).
             floatx4 D[kGC / 4], A[kGC];
             float cb[4], gsub[kGC];
             auto start = [&]() {
 #pragma unroll
                 for (int i = 0; i < kGC / 4; ++i) {
                     const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[scol][4 * i]);
-                    D[i] = sv[i] - floatx4{p4.x, p4.y, p4.z, p4.w};
+                    const floatx4 p = floatx4{p4.x, p4.y, p4.z, p4.w};
+                    D[i] = C::SCALED ? sv[i] - p : -p;
                 }
+            };
+            // v - pred of token t, given what D collects
+            auto error = [&](auto tag, float x) {
+                constexpr int t = decltype(tag)::value;
+                return C::SCALED ? x : sv[t / 4][t % 4] + x;
             };
             start();
 #pragma unroll
@@ -597,7 +621,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                     D[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[S][m], cs, D[m], 0, 0, 0);
             };
             const float rprev0 = rprev;
-            float chk = 0.f, cprev = 0.f, d = D[0][0];
+            float chk = 0.f, cprev = 0.f, d = error(ITag<0>{}, D[0][0]);
             auto keep_r = [&](int t, float rt, float dt) {
                 if constexpr (AX) {   // the backward's recompute: delta of every token
                     if (sact && t < nt && a.delta_out)
@@ -632,16 +656,21 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (JP >= 2) z += dpp_mov<0x128>(z);   // row_ror 8
                 const float iz = rcp_fast(z);
-                const float cs = bdex * iz;   // s c
+                // (one component: r = 1 whatever the exponent; not finite stays so)
+                const float rt = J == 1 ? fmaf(0.0f, slk[t], 1.0f) : ex * iz;
+                const float cs = J == 1 || TP ? bd * rt : bdex * iz;   // s c
                 float dn = 0.f;
-                if constexpr (t + 1 < kGC) dn = fmaf(gsub[t], cs, D[(t + 1) / 4][(t + 1) % 4]);
+                if constexpr (t + 1 < kGC)
+                    dn = error(ITag<(t + 1 < kGC ? t + 1 : 0)>{}, fmaf(gsub[t], cs, D[(t + 1) / 4][(t + 1) % 4]));
                 cb[t & 3] = C::IS * cs;
                 if ((t & 3) == 3)
                     *reinterpret_cast<float4 *>(&sm.c[gs][scst][t - 3]) =
                         make_float4(cb[0], cb[1], cb[2], cb[3]);
-                keep_r(t, ex * iz, d);
-                chk = fmaxf(fmaxf(z, iz), chk);
-                asm volatile("" : "+v"(chk));
+                keep_r(t, rt, d);
+                if constexpr (J > 1) {
+                    chk = fmaxf(fmaxf(z, iz), chk);
+                    asm volatile("" : "+v"(chk));
+                }
                 cprev = cs;
                 d = dn;
             };
@@ -661,7 +690,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 auto slow = [&](auto tag) {
                     constexpr int t = decltype(tag)::value;
                     load_a(t);
-                    const float dd = D[t / 4][t % 4];
+                    const float dd = error(tag, D[t / 4][t % 4]);
                     const float e = TP ? -kS2 * dd * dd : fmaf(C::SCALED ? -dd : -kS2 * dd, dd, slk[t]);
                     float ex = sact ? __builtin_amdgcn_exp2f(e - lane_max(sact ? e : -INFINITY)) : 0.0f;
                     if constexpr (TP) ex *= fmaf(sgs[t], rprev, slk[t]);
@@ -718,15 +747,24 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         };
         auto gates = [&](int m) {
             const int nt = min(kGC, T - m * kGC), sl = m % 3;
-            float c0 = 1.0f, c1 = 1.0f, f0[kGC], f1[kGC];
+            float f0[kGC], f1[kGC];
+            // the running product of 1 + e: in the 24-bit forms in 64 bits (one fused
+            // multiply-add, which runs at the rate of a 32-bit one), so that each E^-1 is
+            // rounded once and not twice a token
+            typename std::conditional<NP == 3, double, float>::type p0 = 1, p1 = 1;
+            auto step = [](auto &p, float e) {
+                if constexpr (NP == 3) p = fma(p, (double)e, p);
+                else p *= 1.0f + e;
+                return (float)p;
+            };
+            float c0 = 1.0f, c1 = 1.0f;
 #pragma unroll
             for (int t = 0; t < kGC; ++t) {
                 // tokens past the end decay nothing
                 const float e0 = __builtin_amdgcn_exp2f(-kLog2e * lo_of(x[t]));
                 const float e1 = __builtin_amdgcn_exp2f(-kLog2e * hi_of(x[t]));
-                c0 *= t < nt ? 1.0f + e0 : 1.0f;
-                c1 *= t < nt ? 1.0f + e1 : 1.0f;
-                f0[t] = c0, f1[t] = c1;
+                f0[t] = c0 = step(p0, t < nt ? e0 : 0.0f);
+                f1[t] = c1 = step(p1, t < nt ? e1 : 0.0f);
             }
             float r0 = rcp_fast(c0), r1 = rcp_fast(c1);
             const bool mine = act && (!(c0 <= kGramEinv) || !(c1 <= kGramEinv));
@@ -902,8 +940,9 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                     for (int y = 0; y < E; ++y) {
                         sm.vs[m & 1][E * p + y][t] = t < nt ? C::S * piece<F32>(rv[x], y) : 0.0f;
                         if constexpr (TP) {
-                            // (tokens past the end keep both priors)
-                            sm.gs[m & 1][E * p + y][t] = t < nt ? 1.0f - sigmoid(piece<F32>(rgk[x], y)) : 1.0f;
+                            // (tokens past the end keep both priors; key_priors turns
+                            // the first into 1 - g^k)
+                            sm.gs[m & 1][E * p + y][t] = t < nt ? sigmoid(piece<F32>(rgk[x], y)) : 0.0f;
                             sm.gq[m % 3][t][E * p + y] = t < nt ? sigmoid(piece<F32>(rgq[x], y)) : 0.0f;
                         }
                     }
@@ -941,7 +980,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 for (int j = 0; j < J; ++j) sm.pq[m & 1][t][j * DB + dd] = J == 1 ? 1.0f : x[j] * iz;
             }
         };
-        // temporal: g^k pi^k of chunk m, pi^k = softmax over j of the key-prior logits
+        // temporal: g^k pi^k and 1 - g^k of chunk m, pi^k = softmax over j of the key-prior logits
         auto key_priors = [&](int m) {
             for (int e = br; e < kGC * DB; e += NBT) {
                 const int t = e % kGC, dd = e / kGC;
@@ -956,7 +995,8 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                     x[j] = __builtin_amdgcn_exp2f(kLog2e * (x[j] - mx));
                     z += x[j];
                 }
-                const float f = (1.0f - sm.gs[m & 1][dd][t]) * rcp_fast(z);
+                const float g = sm.gs[m & 1][dd][t], f = g * rcp_fast(z);
+                sm.gs[m & 1][dd][t] = 1.0f - g;
 #pragma unroll
                 for (int j = 0; j < J; ++j) sm.sq[m & 1][j * DB + dd][t].y = f * x[j];
             }
