@@ -146,8 +146,8 @@ struct GSmem {
     alignas(16) float ei[GT ? C::NEI : 1][GT ? J : 1][GT ? kGC : 1][GT ? C::LP : 4];
     alignas(16) float ec[GT ? C::NEC : 1][GT ? J : 1][GT ? DK : 4];
     int deep[3][J];
-    // for the sequential wave, chunk m in m & 1: {beta, log2(e) key-prior logit}
-    // [column][token] (beta = 0 past the end) and s v [dim][token]; temporal: {beta,
+    // for the sequential wave, chunk m in m & 1: {beta, key-prior logit (times log2(e)
+    // in scaled units)} [column][token] (beta = 0 past the end) and s v [dim][token]; temporal: {beta,
     // g^k pi^k} and 1 - g^k [dim][token]
     alignas(16) float2 sq[2][C::N][kGC + 2];
     alignas(16) float vs[2][DB][kGC + 4];
@@ -641,8 +641,8 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 float ex;
                 if constexpr (TP)   // key prior (1 - g^k) r_{t-1} + g^k pi^k
                     ex = __builtin_amdgcn_exp2f(-kS2 * d * d);
-                else
-                    ex = __builtin_amdgcn_exp2f(fmaf(C::SCALED ? -d : -kS2 * d, d, slk[t]));
+                else   // (log2(e) here: an fp32 logit times it may overflow, see slow)
+                    ex = __builtin_amdgcn_exp2f(fmaf(C::SCALED ? -d : -kS2 * d, d, C::SCALED ? slk[t] : kLog2e * slk[t]));
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (t >= 1) defer(ITag<(t > 0 ? t - 1 : 0)>{}, cprev);
                 __builtin_amdgcn_sched_barrier(0);
@@ -691,8 +691,12 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                     constexpr int t = decltype(tag)::value;
                     load_a(t);
                     const float dd = error(tag, D[t / 4][t % 4]);
-                    const float e = TP ? -kS2 * dd * dd : fmaf(C::SCALED ? -dd : -kS2 * dd, dd, slk[t]);
-                    float ex = sact ? __builtin_amdgcn_exp2f(e - lane_max(sact ? e : -INFINITY)) : 0.0f;
+                    // (fp32 logits up to the type's limits, masks of its lowest value
+                    // among them: log2(e) times the difference from the maximum, not
+                    // a difference of products that may have overflowed)
+                    const float e = TP ? -kS2 * dd * dd : fmaf(C::SCALED ? -dd : -0.5f * dd, dd, slk[t]);
+                    const float em = e - lane_max(sact ? e : -INFINITY);
+                    float ex = sact ? __builtin_amdgcn_exp2f(TP || C::SCALED ? em : kLog2e * em) : 0.0f;
                     if constexpr (TP) ex *= fmaf(sgs[t], rprev, slk[t]);
                     const float iz = rcp_fast(lane_sum(ex));
                     const float cs = sact ? sbeta[t] * dd * ex * iz : 0.0f;
@@ -926,7 +930,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                             sm.sq[m & 1][colE + y][t].x = in ? sigmoid(xb) : 0.0f;
                         else
                             sm.sq[m & 1][colE + y][t] =
-                                make_float2(in ? sigmoid(xb) : 0.0f, in ? kLog2e * xk : 0.0f);
+                                make_float2(in ? sigmoid(xb) : 0.0f, !in ? 0.0f : C::SCALED ? kLog2e * xk : xk);
                     }
                     if constexpr (TP)
                         *reinterpret_cast<uint4 *>(&sm.lk[m & 1][t][colE]) = mask4(rlk[x], in);
