@@ -150,7 +150,8 @@ struct GSmem {
     // in scaled units)} [column][token] (beta = 0 past the end) and s v [dim][token]; temporal: {beta,
     // g^k pi^k} and 1 - g^k [dim][token]
     alignas(16) float2 sq[2][C::N][kGC + 2];
-    alignas(16) float vs[2][DB][kGC + 4];
+    // (row DB: zeros, the idle lanes')
+    alignas(16) float vs[2][DB + 1][kGC + 4];
     alignas(16) float gs[TP ? 2 : 1][TP ? DB : 1][kGC + 4];
     alignas(16) In lk[TP ? 2 : 1][TP ? kGC : 1][TP ? C::N : 8];   // temporal: key-prior logits
     float gq[TP ? 3 : 1][TP ? kGC : 1][TP ? DB : 1];        // temporal: g^q, chunk m in m % 3
@@ -159,7 +160,8 @@ struct GSmem {
     // subdiagonal, [j][s] = that of token s + 1
     alignas(16) float gt[2][J][kGC][kGC];
     alignas(16) float gsub[2][J][kGC];
-    alignas(16) float p[C::N][C::CP];        // chunk-start predictions, times s [column][token]
+    // chunk-start predictions, times s [column][token] (row N: zeros, the idle lanes')
+    alignas(16) float p[C::N + 1][C::CP];
     // coefficients [column][token], chunk m in m & 1 (row N: the idle lanes')
     alignas(16) float c[2][C::N + 1][C::CP];
     float pq[2][kGC][C::NP];                 // pi^q [token][column]
@@ -518,6 +520,9 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         const int sdd = lane / 16 * C::SD + lane % C::SD, sj = lane % 16 / C::SD;
         const bool sact = sdd < DB && sj < J;
         const int scol = sact ? sj * DB + sdd : 0, gj = sact ? sj : 0;
+        // Idle lanes, the padding component of J = 3 among them, which is summed with
+        // the others of its dim, read rows of zeros: another column's v or predictions
+        // would carry what is not finite there to this dim.
         const int scst = sact ? scol : N;
         const bool wres = a.resp && sact;
         auto lane_sum = [](float x) {
@@ -532,7 +537,8 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         };
         float sbeta[kGC], slk[kGC], sgs[TP ? kGC : 1];
         floatx4 sv[kGC / 4];
-        const int vdd = sact ? sdd : 0;
+        const int vdd = sact ? sdd : DB;
+        if (lane < kGC) sm.p[N][lane] = sm.vs[0][DB][lane] = sm.vs[1][DB][lane] = 0.0f;   // (read by this wave alone)
         // r_{t-1} of this lane's column (temporal), and that of the last token
         float rprev = 0.0f, rlast = 0.0f;
         if constexpr (TP) {
@@ -540,7 +546,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 rprev = a.prior_in ? a.prior_in[(((size_t)b * H + h) * 2 * J + sj) * Dv + d0 + sdd]
                                    : 1.0f / J;
         }
-        // beta, key-prior logits and v of chunk m (idle lanes read column 0)
+        // beta, key-prior logits and v of chunk m
         auto seq_inputs = [&](int m) {
 #pragma unroll
             for (int t2 = 0; t2 < kGC; t2 += 2) {
@@ -555,7 +561,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
                 const float4 x = *reinterpret_cast<const float4 *>(&sm.vs[m & 1][vdd][t4]);
                 sv[t4 / 4] = floatx4{x.x, x.y, x.z, x.w};
                 if constexpr (TP) {
-                    const float4 y = *reinterpret_cast<const float4 *>(&sm.gs[m & 1][vdd][t4]);
+                    const float4 y = *reinterpret_cast<const float4 *>(&sm.gs[m & 1][sact ? sdd : 0][t4]);
                     sgs[t4] = sact ? y.x : 0.f, sgs[t4 + 1] = sact ? y.y : 0.f;
                     sgs[t4 + 2] = sact ? y.z : 0.f, sgs[t4 + 3] = sact ? y.w : 0.f;
                 }
@@ -590,7 +596,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             auto start = [&]() {
 #pragma unroll
                 for (int i = 0; i < kGC / 4; ++i) {
-                    const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[scol][4 * i]);
+                    const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[scst][4 * i]);
                     const floatx4 p = floatx4{p4.x, p4.y, p4.z, p4.w};
                     D[i] = C::SCALED ? sv[i] - p : -p;
                 }

@@ -116,3 +116,24 @@ def test_not_finite_reaches_later_tokens_only(form, name, value):
     assert np.array_equal(np.isfinite(o), want)
     assert _rel(o[want], r[0][want]) <= TOL
     assert np.array_equal(np.isfinite(a[1]), np.isfinite(r[1]))
+
+
+# the same for every component count (J = 3 has a padding lane in each dim) and for the
+# first dim of a block, which idle lanes might read
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("J", [1, 2, 3])
+@pytest.mark.parametrize("dim", [0, 8, 15])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_not_finite_stays_in_its_dim(form, J, dim, value):
+    B, H, T, Dk, Dv, at = 1, 2, 45, 32, 16, 23
+    inp = workloads.iid_inputs(B, H, T, Dk, Dv, J, dtype="f32", seed=1595, state_std=0.1)
+    tmp = workloads.temporal_inputs(B, H, T, Dv, J, dtype="f32", seed=1595, prior_state=True)
+    dec = workloads.gated_inputs(B, H, T, Dk, J, dtype="f32", seed=1595, mean=2.0)["decay"]
+    inp["v"][0, at, 1, dim] = value
+    a, r = _run(form, inp, tmp, dec, "auto"), _run(form, inp, tmp, dec, "recurrent")
+    want = np.ones(a[0].shape, bool)
+    want[0, at:, 1, dim] = False
+    assert np.array_equal(np.isfinite(r[0]), want)   # (the token scan)
+    assert np.array_equal(np.isfinite(a[0]), want)
+    assert _rel(a[0][want], r[0][want]) <= TOL
+    assert np.array_equal(np.isfinite(a[1]), np.isfinite(r[1]))
