@@ -495,7 +495,25 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
                 gv[m] = s2 >= tl ? sGkqT[s2][tl] : 0.0f;
                 yv[m] = cv ? sY[sl][s2][col] : 0.0f;
             }
+            // A dy that is not finite (a dL/do that is not) would reach the tokens after
+            // its own too, as 0 times it: with fp32 inputs, whose vector-ALU sums left
+            // those terms out, such ones are taken out of the product and the column's
+            // tokens up to the last of them set to NaN.
+            int last = -1;
+            const bool odd = !IBF && __builtin_amdgcn_ballot_w64(!(fabsf((yv[0] + yv[1]) + (yv[2] + yv[3])) < INFINITY)) != 0;
+            if (odd) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if (!(fabsf(yv[m]) < INFINITY)) yv[m] = 0.0f, last = 4 * lg + m;
+                last = max(last, __shfl_xor(last, 16));
+                last = max(last, __shfl_xor(last, 32));
+            }
             acc = mmp(kop<4, PE>(gv), kop<4, PE>(yv), acc);
+            if (odd) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (4 * lg + r <= last) acc[r] = NAN;
+            }
             if (cv) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) sBase[4 * lg + r][col] = acc[r];

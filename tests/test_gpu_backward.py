@@ -182,3 +182,36 @@ def test_backward_lm_batch_sampled_head():
     errs["state"] = head_rel_err(res[6][b:b + 1, h:h + 1].cpu().numpy(), ref["state"], "state")
     print(" ".join("%s %.2e" % kv for kv in errs.items()))
     assert all(v <= 2e-2 for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("J,Dk,Dv", [(1, 32, 64), (2, 64, 32), (3, 16, 16), (4, 64, 64), (8, 32, 16)])
+@pytest.mark.parametrize("at", [0, 20, 31, 32])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_not_finite_grad_reaches_earlier_tokens_only(J, Dk, Dv, at, value):
+    """fp32: dL/do that is not finite at one token and output dim leaves the gradients of the
+    later tokens, also those of its own chunk, and of the other dims as they are."""
+    import torch
+    import paper_2609_39034_amd as sw
+    B, H, T, d = 1, 2, 41, 0 if Dv == 16 else 5
+    inp = workloads.iid_inputs(B, H, T, Dk, Dv, J, dtype="f32", seed=1650 + J, state_std=0.1)
+    dev = to_device(inp, "f32")
+    go = torch.from_numpy(np.random.default_rng(1650).standard_normal((B, T, H, Dv)).astype(np.float32)).cuda()
+    clean = [x.cpu().numpy() for x in sw.backward(*(dev[n] for n in NAMES), dev["state"], go)]
+    go[0, at, 1, d] = value
+    got = [x.cpu().numpy() for x in sw.backward(*(dev[n] for n in NAMES), dev["state"], go)]
+    for name, x, y in zip(GRADS + ("state",), got, clean):
+        free = np.zeros(x.shape, bool)          # what the value may reach
+        if name == "state":
+            free[0, 1, ..., d] = True
+        elif name == "q":
+            free[0, at, 1] = True
+        elif name == "k":
+            free[0, :at + 1, 1] = True
+        elif name == "lq":
+            free[0, at, 1, ..., d] = True
+        else:
+            free[0, :at + 1, 1, ..., d] = True
+        assert np.isfinite(x[~free]).all(), name
+        assert np.abs(x - y)[~free].max() <= 1e-5 * max(np.abs(y).max(), 1e-6), name
+        if name in ("v", "lb"):
+            assert not np.isfinite(x[free]).any(), name
