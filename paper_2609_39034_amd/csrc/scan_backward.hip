@@ -86,7 +86,6 @@ constexpr int chunk_tile_dims() { return J == 1 ? 16 : J == 3 ? 8 : 32 / J; }
 // J=4: the launch took 172 us with fp32 products on the vector ALUs, in five steps
 // between barriers).
 constexpr int kRC = 16;   // tokens per chunk of the reverse scan
-constexpr int kRT = 512;  // threads of a reverse-scan block: the sequential wave and seven others
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -170,8 +169,8 @@ __device__ __forceinline__ void st_row(float *p, const float (&v)[J]) {
 //   C  the base of chunk n-1 from the new E (one wave per 16-column tile);
 //      chunk n's outputs on waves 2 and up when there are two tiles or fewer,
 //      else in B.
-template <int DK, int J, int DB, bool IBF>
-__global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
+template <int DK, int J, int DB, bool IBF, int RT>
+__global__ __launch_bounds__(RT) void reverse_chunk_kernel(BackwardArgs a) {
     constexpr int JP = J == 3 ? 4 : J;   // lanes per output dim (J = 3 padded)
     constexpr int N = J * DB;            // columns, col = j * DB + dd
     constexpr int NL = JP * DB;          // sequential lanes, lane = dd * JP + j
@@ -197,7 +196,7 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
     // matrix-core lane coordinates: row / column tl, k slot lg
     const int wv = __builtin_amdgcn_readfirstlane(tid / 64), tl = lane % 16, lg = lane / 16;
     constexpr int NTC = (N + 15) / 16;    // 16-column tiles
-    constexpr int NWV = kRT / 64;         // waves
+    constexpr int NWV = RT / 64;         // waves
     constexpr int KM = DK >= 32 ? 8 : 4;  // k values per lane: 32- or 16-deep products
     const int H = f.H, T = f.T, Dv = f.Dv;
     // Workgroups go to the eight XCDs (each with its own L2) round-robin by
@@ -223,7 +222,7 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
     const size_t sbase = ((size_t)b * H + h) * J * DK * Dv;
 
     // E = dL/dW_T (or 0), [i][col]
-    for (int e = tid; e < DK * N; e += kRT) {
+    for (int e = tid; e < DK * N; e += RT) {
         const int i = e / N, col = e % N, j = col / DB, dd = col % DB;
         sE[i][col] = a.grad_state ? a.grad_state[sbase + ((size_t)j * DK + i) * Dv + d0 + dd] : 0.0f;
     }
@@ -234,12 +233,12 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
 
     // Each chunk's HBM inputs are fetched into registers while a later chunk
     // computes: K and Q rows as float4, and per (token, output dim) the J
-    // errors and logits and dL/do.  The staging threads (F0 .. kRT - 1)
+    // errors and logits and dL/do.  The staging threads (F0 .. RT - 1)
     // load them and later stage them.  Every such thread loads every item it
     // owns, from a clamped row (the chunk's last token, the last item), with the
     // input dtype fixed at compile time: no load sits behind a branch (a load
     // there is waited for at the join); staging zeroes what lies past the end.
-    constexpr int F0 = 64, FT = kRT - F0;
+    constexpr int F0 = 64, FT = RT - F0;
     constexpr int NKQ = (kRC * (DK / 4) + FT - 1) / FT;
     constexpr int NSC = (kRC * DB + FT - 1) / FT;
     uint4 pk[NKQ] = {}, pq[NKQ] = {};   // (bf16: halves x and y)
@@ -476,7 +475,7 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
     // base_t = k_t . E + sum_{s>=t} (k_t . q_s) dy_s for the chunk in slot sl: a
     // 16-column tile per wave
     auto base = [&](int sl) {
-        for (int ct = wv; ct < NTC; ct += kRT / 64) {
+        for (int ct = wv; ct < NTC; ct += RT / 64) {
             const int col = 16 * ct + tl;
             const bool cv = col < N;
             floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -666,11 +665,11 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
         }
     };
     constexpr ITag<64> kF1{};               // the staging threads
-    constexpr ITag<kRT - 64> kN1{};
+    constexpr ITag<RT - 64> kN1{};
     constexpr ITag<0> kF0{};                // every thread
-    constexpr ITag<kRT> kN0{};
+    constexpr ITag<RT> kN0{};
     constexpr ITag<128> kF2{};              // waves 2 and up
-    constexpr ITag<kRT - 128> kN2{};
+    constexpr ITag<RT - 128> kN2{};
 
 
     if (NCH > 0) {
@@ -717,7 +716,7 @@ __global__ __launch_bounds__(kRT) void reverse_chunk_kernel(BackwardArgs a) {
     }
     block_sync_lds();
     if (a.dstate) {
-        for (int e = tid; e < J * DK * DB; e += kRT) {
+        for (int e = tid; e < J * DK * DB; e += RT) {
             const int j = e / (DK * DB), i = (e / DB) % DK, dd = e % DB;
             a.dstate[sbase + ((size_t)j * DK + i) * Dv + d0 + dd] = sE[i][j * DB + dd];
         }
@@ -1096,12 +1095,26 @@ hipError_t launch_reverse(const BackwardArgs &a, hipStream_t stream) {
         return hipErrorInvalidValue;
     } else {
         const dim3 grid((unsigned)((a.f.Dv / DB) * a.f.H * a.f.B));
-        if (a.f.in_bf16)
-            hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, true>), grid, dim3(kRT), 0,
-                               stream, a);
-        else
-            hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, false>), grid, dim3(kRT), 0,
-                               stream, a);
+        auto go = [&](auto rt) {
+            constexpr int RT = decltype(rt)::value;
+            if (a.f.in_bf16)
+                hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, true, RT>), grid, dim3(RT), 0, stream, a);
+            else
+                hipLaunchKernelGGL((reverse_chunk_kernel<DK, J, DB, false, RT>), grid, dim3(RT), 0, stream, a);
+        };
+        // Eight waves a block, the sequential wave and seven others, fill a compute unit
+        // with one block (over 128 registers a lane).  Narrow blocks of one component
+        // have little for seven waves to do: from 257 blocks on four waves, two blocks to
+        // a unit, are faster (T=128, whole backward, 288 blocks: bf16 Dk=32 Dv=32 76.9 -> 67.3
+        // us, Dk=64 Dv=16 79.0 -> 66.8, fp32 107.3 -> 94.7 and 102.7 -> 87.4).  With two
+        // components or 64 columns they are 7 to 23% slower (D=64: J=4 128.6 -> 152.3,
+        // J=1 115.9 -> 142.7).
+        if constexpr (J == 1 && DB <= 32)
+            if (grid.x > 256) {
+                go(ITag<256>{});
+                return hipGetLastError();
+            }
+        go(ITag<512>{});
         return hipGetLastError();
     }
 }
@@ -1121,12 +1134,15 @@ hipError_t launch_bwd_dk_j(const BackwardArgs &a, hipStream_t stream) {
                    : chunk_f32_preferred(fa) ? launch_scan_chunk_f32(fa, stream)
                                              : launch_scan_direct_aux(fa, stream);
     if (e != hipSuccess) return e;
-    // reverse scan: 64 sequential lanes per block (DB = 64 / JP output dims), or
-    // half as many (and twice the blocks) while the grid would leave compute
-    // units idle
+    // reverse scan: 64 sequential lanes per block (DB = 64 / JP output dims), or half as
+    // many and twice the blocks where those still run in one round, one to a compute
+    // unit.  A block's time hardly depends on its width, so a second round costs more than
+    // the idle units of a grid of 129 to 255 wide blocks (T=256 Dv=64, 192 wide blocks against 384
+    // narrow ones: bf16 J=4 Dk=32 118 against 148 us, J=3 Dk=64 116 against 156; fp32 J=4
+    // Dk=64 203 against 236).
     constexpr int JP = J == 3 ? 4 : J;
     int db = 64 / JP < f.Dv ? 64 / JP : f.Dv;
-    if ((long)(f.Dv / db) * f.H * f.B < 256 && db >= 16) db /= 2;
+    if ((long)(f.Dv / db) * f.H * f.B <= 128 && db >= 16) db /= 2;
     switch (db) {
         case 64: e = launch_reverse<DK, J, 64>(a, stream); break;
         case 32: e = launch_reverse<DK, J, 32>(a, stream); break;
