@@ -574,12 +574,13 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
     // Roles: waves 0 .. NW-1 hold the state tiles (matrix-core products);
     // wave NW is the sequential wave; with NH > 0, wave NW+1 forms the chunks' Gram
     // matrices and waves NW+2 .. NW+NH do the per-chunk bookkeeping (transfers,
-    // priors, input prep, outputs); the tile waves do both when NH = 0.
+    // priors, input prep, outputs); with NH = 1 that one wave does both, with NH = 0
+    // the tile waves do.
     const bool tile = w < NW;
-    const bool book = NH == 0 ? tile : w > NW + 1;    // this wave does the bookkeeping
-    constexpr int NBW = NH == 0 ? NW : NH - 1;        // bookkeeping waves
+    const bool book = NH == 0 ? tile : w > NW + (NH > 1);   // this wave does the bookkeeping
+    constexpr int NBW = NH == 0 ? NW : NH == 1 ? 1 : NH - 1;   // bookkeeping waves
     constexpr int NBT = 64 * NBW;                     // bookkeeping threads
-    const int bw = NH == 0 ? w : w - (NW + 2);        // index among them
+    const int bw = NH == 0 ? w : w - (NW + 1 + (NH > 1));   // index among them
     // The compiler cannot bound bt (the wave index comes from readfirstlane), so
     // loops strided by NBT count 0 .. ceil(n / NBT) from bt and stop at n: a
     // trip count it can see, and fully unrolled loops.
@@ -1407,9 +1408,9 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
         constexpr bool DT = true, DBK = false, DG = false;
 #include "scan_pipe_mfma_side.inc"
     } else if (gwave) {
-        constexpr bool DT = false, DBK = false, DG = true;
+        constexpr bool DT = false, DBK = NH == 1, DG = true;
 #include "scan_pipe_mfma_side.inc"
-    } else {
+    } else if constexpr (NH > 1) {
         constexpr bool DT = false, DBK = true, DG = false;
 #include "scan_pipe_mfma_side.inc"
     }
@@ -1425,26 +1426,42 @@ hipError_t launch_cfg(const LayerArgs &a, const NewtonArgs &na, hipStream_t stre
     constexpr size_t lds = sizeof(PSmem<DK, J, DB, MD>);
     static_assert(lds <= 160 * 1024, "LDS");
     const long blocks = (long)(a.Dv / DB) * a.H * a.B;
-    // Enough blocks to put two on every compute unit (LDS permitting): their
-    // waves hide each other's latencies, so the tile waves keep the
-    // bookkeeping.  Otherwise helper waves take it over: the Gram wave and four
-    // for the rest.  (With three, the last of them reaches the chunk's middle
-    // barrier after the sequential wave: 145 against 139 us at B=4 H=8 T=2048
-    // D=64 J=4, 480 against 430 us at B=2 H=16 T=4096 D=128 J=4; six are 1%
-    // faster at that shape and 11% slower in the temporal form.)
-    // (a block over 80 KB of LDS is never two to a compute unit: only the
-    // variant with helpers is built for it)
-    constexpr int NH = 5;
-    if constexpr (lds <= 80 * 1024) {
-        if (blocks >= 512) {
-            hipLaunchKernelGGL((scan_pipe_kernel<DK, J, DB, MD, 0>), dim3((unsigned)blocks),
-                               dim3(64 * (C::NW + 1)), 0, stream, a, na);
-            return hipGetLastError();
+    // Waves beside the tile waves and the sequential one.  While a compute unit gets one
+    // block, the Gram wave and four for the rest.  (With three, the last of them reaches
+    // the chunk's middle barrier after the sequential wave: 145 against 139 us at B=4 H=8
+    // T=2048 D=64 J=4, 480 against 430 us at B=2 H=16 T=4096 D=128 J=4; six are 1%
+    // faster at that shape and 11% slower in the temporal form.)  Where two blocks'
+    // LDS fit and the grid has more than one for every unit, fewer waves, so that their
+    // registers (160 a lane, three waves to a SIMD) fit too.  T=256, 320 blocks / 512 / 768:
+    //   one tile wave: a Gram wave and one for the rest, three blocks to a unit (Dk=64 J=1
+    //     Dv=16: 23.7 / 25.1 / 30.3 us, with four for the rest 36.8 / 37.2 / 54.4); or
+    //     one wave for both where four fit (Dk=16, 1,024 blocks: 37.0 against 45.8)
+    //   two: one wave for both, two blocks to a unit (Dk=16 J=2 Dv=16: 29.2 / 30.1 /
+    //     54.0; with five waves 38.2 / 38.8 / 56.8, with none 35.0 / 36.2 / 58.6).  The
+    //     temporal form's one wave is late from the third block on (1.10 to 1.17 of the time
+    //     with none): none there, the tile waves do both
+    //   three and four: none, from 512 blocks on
+    // (a block over 80 KB of LDS is never two to a compute unit)
+    auto go = [&](auto nh) {
+        constexpr int NH = decltype(nh)::value;
+        hipLaunchKernelGGL((scan_pipe_kernel<DK, J, DB, MD, NH>), dim3((unsigned)blocks),
+                           dim3(64 * (C::NW + 1 + NH)), 0, stream, a, na);
+        return hipGetLastError();
+    };
+    if constexpr (lds <= 80 * 1024 && MD != 1 && C::NW <= 2) {
+        if constexpr (C::NW == 1) {
+            if constexpr (lds <= 40 * 1024)
+                if (blocks > 768) return go(IntTag<1>{});
+            if (blocks > 256) return go(IntTag<2>{});
+        } else {
+            if (blocks > 256 && (MD == 0 || blocks <= 512)) return go(IntTag<1>{});
+            if constexpr (MD == 2)
+                if (blocks > 512) return go(IntTag<0>{});
         }
+    } else if constexpr (lds <= 80 * 1024) {
+        if (blocks >= 512) return go(IntTag<0>{});
     }
-    hipLaunchKernelGGL((scan_pipe_kernel<DK, J, DB, MD, NH>), dim3((unsigned)blocks),
-                       dim3(64 * (C::NW + 1 + NH)), 0, stream, a, na);
-    return hipGetLastError();
+    return go(IntTag<5>{});
 }
 
 template <int DK, int MD>
