@@ -217,6 +217,11 @@ struct PCfg {
     __device__ static constexpr int srow(int col) { return col + XS * (col / DB); }
 };
 
+// The responsibilities' buffer (sm.r) is dynamic LDS, given only to the calls that keep
+// r or delta, where the rest of the block's LDS then fits a compute unit twice.
+template <int DK, int J, int MD>
+constexpr bool dynamic_r() { return MD == 0 && J == 3 && DK <= 32; }
+
 // MD: 0 exact scan, 1 Newton sweeps (App. D), 2 exact scan of Temporal SwiLA
 // (App. B.3).
 template <int DK, int J, int DB, int MD>
@@ -257,7 +262,8 @@ struct PSmem {
     // (C::prow(N): the idle lanes' row of c)
     float p[2][C::NRP][kTP];
     float c[2][C::NRP + 1][kTP];
-    float r[NT ? 1 : 2][kC][C::NP];  // responsibilities (exact mode)
+    static constexpr bool DR = dynamic_r<DK, J, MD>();
+    float r[NT || DR ? 1 : 2][DR ? 1 : kC][C::NP];  // responsibilities (exact mode)
     float py[2][kC][C::NP];    // pi^q * retrieval
     int flag;                  // Newton: this sweep met the tolerance
     int near;                  // Newton: its change was within 4 tol (the next may be the last)
@@ -559,6 +565,12 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
     constexpr int IT = C::IT, N = C::N, NW = C::NW, JP = C::JP;
     constexpr bool NT = MD == 1, TP = MD == 2;
     __shared__ PSmem<DK, J, DB, MD> sm;
+    extern __shared__ __align__(16) float dynamic_lds[];
+    // r (or delta) of token t, column c, chunk parity pr
+    auto rbuf = [&](int pr, int t, int c) -> float & {
+        if constexpr (dynamic_r<DK, J, MD>()) return dynamic_lds[(pr * kC + t) * C::NP + c];
+        else return sm.r[pr][t][c];
+    };
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&sm;
 
     const int tid = threadIdx.x;
@@ -1019,7 +1031,7 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
             if (m * kC + t < T)
                 *reinterpret_cast<float4 *>(
                     rdst + ((((size_t)b * T + m * kC + t) * H + h) * J + cc / DB) * Dv + d0 +
-                    cc % DB) = *reinterpret_cast<const float4 *>(&sm.r[pr][t][cc]);
+                    cc % DB) = *reinterpret_cast<const float4 *>(&rbuf(pr, t, cc));
           }
         }
     };
@@ -1263,10 +1275,10 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
                                     make_float4(cb[0], cb[1], cb[2], cb[3]);
                             if constexpr (R == 1) {
                                 const float rt = ex * iz;
-                                sm.r[pr][t][bsto] = rt;
+                                rbuf(pr, t, bsto) = rt;
                                 if constexpr (TP) rprev = rt;
                             }
-                            if constexpr (R == 2) sm.r[pr][t][bsto] = kInvS * d;
+                            if constexpr (R == 2) rbuf(pr, t, bsto) = kInvS * d;
                             chk = fmaxf(fmaxf(z, iz), chk);
                             asm volatile("" : "+v"(chk));
                             cprev = cs;
@@ -1289,10 +1301,10 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
                             sm.c[pr][C::prow(bsto)][t] = cs;
                             if constexpr (R == 1) {
                                 const float rt = ex * iz;
-                                sm.r[pr][t][bsto] = rt;
+                                rbuf(pr, t, bsto) = rt;
                                 if constexpr (TP) rprev = rt;
                             }
-                            if constexpr (R == 2) sm.r[pr][t][bsto] = kInvS * dd;
+                            if constexpr (R == 2) rbuf(pr, t, bsto) = kInvS * dd;
                         };
                         const float rprev0 = rprev;
                         token(IntTag<0>{}), token(IntTag<1>{}), token(IntTag<2>{}), token(IntTag<3>{});
@@ -1392,7 +1404,7 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
             // r of the last token: part 0 of the prior state
             if (bact && a.prior_out)
                 a.prior_out[(((size_t)b * H + h) * 2 * J + bj) * Dv + d0 + bdl] =
-                    sm.r[(NCH - 1) & 1][T - 1 - (NCH - 1) * kC][bsto];
+                    rbuf((NCH - 1) & 1, T - 1 - (NCH - 1) * kC, bsto);
         }
         return;
     }
@@ -1440,12 +1452,15 @@ hipError_t launch_cfg(const LayerArgs &a, const NewtonArgs &na, hipStream_t stre
     //     54.0; with five waves 38.2 / 38.8 / 56.8, with none 35.0 / 36.2 / 58.6).  The
     //     temporal form's one wave is late from the third block on (1.10 to 1.17 of the time
     //     with none): none there, the tile waves do both
-    //   three and four: none, from 512 blocks on
+    //   three and four: none, from 512 blocks on (J = 3: Dk=16, 512 blocks 35.9 against
+    //     42.2, but with r kept its LDS does not fit twice)
     // (a block over 80 KB of LDS is never two to a compute unit)
+    constexpr bool DR = dynamic_r<DK, J, MD>();
+    const size_t dyn = DR && (a.resp || a.delta_out) ? 2 * kC * C::NP * sizeof(float) : 0;
     auto go = [&](auto nh) {
         constexpr int NH = decltype(nh)::value;
         hipLaunchKernelGGL((scan_pipe_kernel<DK, J, DB, MD, NH>), dim3((unsigned)blocks),
-                           dim3(64 * (C::NW + 1 + NH)), 0, stream, a, na);
+                           dim3(64 * (C::NW + 1 + NH)), dyn, stream, a, na);
         return hipGetLastError();
     };
     if constexpr (lds <= 80 * 1024 && MD != 1 && C::NW <= 2) {
@@ -1459,7 +1474,7 @@ hipError_t launch_cfg(const LayerArgs &a, const NewtonArgs &na, hipStream_t stre
                 if (blocks > 512) return go(IntTag<0>{});
         }
     } else if constexpr (lds <= 80 * 1024) {
-        if (blocks >= 512) return go(IntTag<0>{});
+        if (blocks >= 512 && lds + dyn <= 80 * 1024) return go(IntTag<0>{});
     }
     return go(IntTag<5>{});
 }
