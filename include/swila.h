@@ -67,7 +67,7 @@ enum swila_dtype { SWILA_F32 = 0, SWILA_BF16 = 1 };
 enum swila_algo {
     SWILA_ALGO_AUTO = 0,        /* CHUNK_EXACT for bf16 inputs with J <= 8, else RECURRENT;
                                    for fp32 inputs with J <= 4 and J * Dk <= 256, where the
-                                   grid is small enough for it to be faster, the recurrence
+                                   length and the grid make it faster, the recurrence
                                    16 tokens at a time on the matrix cores with products that
                                    keep all 24 bits of their operands (every fp32 operand in
                                    three bf16 parts) */
@@ -294,7 +294,8 @@ typedef struct swila_gated {
  *     or without temporal priors, J * Dk <= 1024).
  *   SWILA_ALGO_AUTO: CHUNK_EXACT where it applies; with temporal priors the
  *     chunk form on products that keep all 24 bits of their fp32 operands, for
- *     bf16 inputs, J <= 4 and J * Dk <= 256; fp32 inputs as in swila_forward;
+ *     bf16 inputs, J <= 4 and J * Dk <= 256, on the lengths and grids where it is
+ *     faster; fp32 inputs as in swila_forward;
  *     else RECURRENT.
  *   SWILA_ALGO_NEWTON returns SWILA_EUNSUPPORTED.
  * T == 0 copies the states.

@@ -90,7 +90,11 @@ hipError_t launch_scan_gated_chunk(const LayerArgs &a, hipStream_t stream);
 // J = 4, Dk = 128 without temporal priors.
 hipError_t launch_scan_gated_chunk_wide(const LayerArgs &a, hipStream_t stream);
 // The same kernel for fp32 inputs (plain, temporal and gated forms), with every
-// fp32 operand in three bf16 parts: J <= 4, J * Dk <= 256, no backward support.
+// fp32 operand in three bf16 parts: J <= 4, J * Dk <= 256.  The plain form writes
+// a.delta_out and a.ckpt where they are set (o may then be nullptr): the backward's
+// recompute.  chunk_pays: whether the form in three parts (this one, and bf16 inputs
+// with gates and temporal priors) is faster than the token-by-token scan.
+bool chunk_pays(const LayerArgs &a);
 bool chunk_f32_supported(const LayerArgs &a);
 bool chunk_f32_preferred(const LayerArgs &a);
 hipError_t launch_scan_chunk_f32(const LayerArgs &a, hipStream_t stream);

@@ -506,7 +506,8 @@ int swila_forward_gated(const swila_shape *shape, const swila_opts *opts, const 
                     "the gated chunk form takes bf16 inputs without temporal priors, J <= 4 "
                     "and J * Dk <= 512 (J=%d, Dk=%d)",
                     shape->J, shape->Dk);
-    const bool use_chunk = chunk_ok && opts->algo != SWILA_ALGO_RECURRENT;
+    const bool use_chunk =
+        chunk_ok && opts->algo != SWILA_ALGO_RECURRENT && (!temporal || swila::chunk_pays(a));
     if (!use_chunk && shape->J * shape->Dk > swila::kMaxGatedJDk)
         return fail(SWILA_EUNSUPPORTED, "gated forward: J * Dk = %d exceeds %d",
                     shape->J * shape->Dk, swila::kMaxGatedJDk);

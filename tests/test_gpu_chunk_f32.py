@@ -76,6 +76,9 @@ FORMS = ["plain", "temporal", "gated", "gated_temporal"]
     (1, 2, 49, 128, 16, 1, 0.1, 2.0, False), (1, 1, 64, 64, 32, 3, 0.1, 3.0, True),
     (16, 16, 19, 16, 16, 4, 0.1, 2.0, True), (8, 32, 18, 64, 16, 2, 0.1, 2.0, False),
     (1, 2, 40, 64, 32, 4, 0.2, -4.0, True), (1, 2, 50, 128, 16, 2, 0.2, -3.0, True),
+    # lengths from which AUTO takes the chunk form (the two meet later with fewer components)
+    (1, 3, 31, 128, 32, 2, 0.2, 2.0, False), (1, 2, 127, 128, 16, 1, 0.1, 2.0, False),
+    (16, 16, 24, 64, 16, 2, 0.1, 2.0, False), (1, 2, 95, 64, 16, 1, 0.1, -3.0, True),
 ])
 def test_chunk_matches_token_scan(form, B, H, T, Dk, Dv, J, std, mean, prior):
     _check(form, B, H, T, Dk, Dv, J, std, mean, prior, 1500 + T + Dk + J)

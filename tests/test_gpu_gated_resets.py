@@ -29,7 +29,7 @@ def _rel(x, y):
 def _check(dtype, temporal, Dk, J, close):
     import torch
     import paper_2609_39034_amd as sw
-    B, H, T, Dv = 1, 3, 43, 16
+    B, H, T, Dv = 1, 3, 127 if (Dk, J) == (128, 1) else 43, 16   # (a length that AUTO gives the chunk form)
     inp = workloads.iid_inputs(B, H, T, Dk, Dv, J, dtype=dtype, seed=1700 + Dk + J, state_std=0.2)
     dec = workloads.gated_inputs(B, H, T, Dk, J, dtype=dtype, seed=1700, mean=2.0)["decay"]
     close(dec)

@@ -67,6 +67,10 @@ def _check(case, tol=TOL, **kw):
     (1, 2, 49, 128, 16, 1, 0.1, 2.0, False), (1, 1, 64, 64, 32, 3, 0.1, 3.0, True),
     (8, 16, 35, 16, 32, 4, 0.1, 2.0, True), (16, 16, 18, 64, 16, 2, 0.1, 2.0, False),
     (1, 2, 40, 64, 32, 4, 0.2, -4.0, True), (1, 2, 50, 128, 16, 2, 0.2, -3.0, True),
+    # lengths from which AUTO takes the chunk form (the two meet later with fewer components)
+    (1, 1, 6, 64, 16, 4, 0.0, 2.0, False), (1, 3, 31, 128, 32, 2, 0.2, 2.0, False),
+    (1, 2, 127, 128, 16, 1, 0.1, 2.0, False), (16, 16, 24, 64, 16, 2, 0.1, 2.0, False),
+    (2, 2, 8, 32, 64, 3, 0.1, 0.0, True), (1, 2, 95, 64, 16, 1, 0.1, -3.0, True),
 ])
 def test_chunk_matches_token_scan(B, H, T, Dk, Dv, J, std, mean, prior):
     _check(_inputs(B, H, T, Dk, Dv, J, 1300 + T + Dk + J, std, mean, prior))
@@ -103,6 +107,20 @@ def test_chained_calls_and_float_output():
     second = _gpu(i2, t2, np.ascontiguousarray(dec[:, cut:]), "auto", out_dtype=torch.float32)
     assert _rel(np.concatenate([first[0], second[0]], 1), whole[0]) <= TOL
     assert _rel(second[1], whole[1]) <= TOL and _rel(second[2], whole[2]) <= TOL
+
+
+@pytest.mark.parametrize("B,H,T,Dk,Dv,J,chunk", [
+    (1, 2, 1, 64, 16, 4, False), (1, 2, 5, 64, 16, 4, False), (1, 2, 7, 32, 16, 3, False),
+    (1, 2, 17, 64, 32, 2, False), (1, 2, 17, 64, 64, 1, False), (1, 2, 64, 128, 16, 1, False),
+    (17, 16, 40, 64, 16, 1, False), (33, 16, 20, 16, 16, 2, False), (33, 16, 32, 16, 16, 4, False),
+    (1, 2, 32, 64, 16, 4, True), (1, 2, 48, 64, 16, 1, True), (33, 16, 144, 64, 16, 4, True),
+])
+def test_auto_takes_the_faster_form(B, H, T, Dk, Dv, J, chunk):
+    """Short calls, and large grids of few components or short keys, on the token scan (its
+    result to the bit); the others on the chunk form (other roundings)."""
+    case = _inputs(B, H, T, Dk, Dv, J, 1380 + T + J, 0.1, 2.0, True)
+    same = all(np.array_equal(x, y) for x, y in zip(_gpu(*case, "auto"), _gpu(*case, "recurrent")))
+    assert same != chunk
 
 
 def test_other_shapes_keep_the_token_scan():
