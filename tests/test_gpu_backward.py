@@ -215,3 +215,14 @@ def test_not_finite_grad_reaches_earlier_tokens_only(J, Dk, Dv, at, value):
         assert np.abs(x - y)[~free].max() <= 1e-5 * max(np.abs(y).max(), 1e-6), name
         if name in ("v", "lb"):
             assert not np.isfinite(x[free]).any(), name
+
+
+@pytest.mark.parametrize("B,H,T,Dk,Dv,J", [(1, 2, 33, 128, 16, 4), (16, 16, 35, 128, 16, 4),
+                                           (16, 16, 33, 64, 32, 8), (1, 2, 15, 32, 32, 2), (2, 2, 10, 64, 16, 1)])
+def test_backward_token_scan_recompute(B, H, T, Dk, Dv, J):
+    """fp32 calls whose forward is recomputed by the token-by-token scan (J * Dk > 256, J > 4
+    or too short for the chunk form), on grids under and over its 256-block line."""
+    heads = [(0, 0), (B - 1, H - 1), (B // 2, H // 2)]
+    errs = _run(B, H, T, Dk, Dv, J, "f32", 0.1, True, seed=760 + J, heads=heads)
+    print(errs)
+    assert all(v <= tol_for("f32") for v in errs.values()), errs

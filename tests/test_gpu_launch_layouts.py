@@ -22,7 +22,7 @@ def _run(inp, gated_decay=None):
         res = sw.forward(*(dev[n] for n in NAMES), dev["state"], algo="recurrent")
     else:
         dec = torch.from_numpy(np.ascontiguousarray(gated_decay)).cuda()
-        res = sw.forward_gated(*(dev[n] for n in NAMES), dec, dev["state"])
+        res = sw.forward_gated(*(dev[n] for n in NAMES), dec, dev["state"], algo="recurrent")
     torch.cuda.synchronize()
     return [x.cpu().numpy().astype(np.float64) for x in res[:2]]
 

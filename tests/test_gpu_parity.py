@@ -58,6 +58,13 @@ def test_small_shapes(B, H, T, Dk, Dv, J, dtype, std):
     _check(inp, dtype)
 
 
+@pytest.mark.parametrize("B,H,T,Dk,Dv,J,dtype,std", [c for c in SMALL if c[6] == "f32"])
+def test_small_shapes_token_scan(B, H, T, Dk, Dv, J, dtype, std):
+    """The fp32 shapes on the token-by-token scan, where AUTO picks the chunk form."""
+    inp = workloads.iid_inputs(B, H, T, Dk, Dv, J, dtype=dtype, seed=100 + T + J, state_std=std)
+    _check(inp, dtype, algo="recurrent")
+
+
 # every (Dk, J, column block) instantiation of the matrix-core chunk scan, with
 # ragged last chunks, and the token-by-token scan on the same bf16 inputs
 CHUNK = [

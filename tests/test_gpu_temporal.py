@@ -71,6 +71,24 @@ def test_temporal_forward(B, H, T, Dk, Dv, J, dtype, std, with_prior, gs):
     assert eo <= tol and es <= tol and er <= tol and ep <= tol
 
 
+@pytest.mark.parametrize("B,H,T,Dk,Dv,J,dtype,std,with_prior,gs",
+                         [c for c in CASES if c[6] == "f32"])
+def test_temporal_forward_token_scan(B, H, T, Dk, Dv, J, dtype, std, with_prior, gs):
+    """The fp32 cases on the token-by-token scan, where AUTO picks the chunk form."""
+    seed = 300 + T + J
+    inp = workloads.iid_inputs(B, H, T, Dk, Dv, J, dtype=dtype, seed=seed, state_std=std)
+    tmp = workloads.temporal_inputs(B, H, T, Dv, J, dtype=dtype, seed=seed, gate_scale=gs,
+                                    prior_state=with_prior)
+    o, s, p, r = _run_gpu(inp, tmp, dtype, algo="recurrent")
+    ref = _run_oracle(inp, tmp)
+    tol = tol_for(dtype)
+    eo, es, er = (head_rel_err(o, ref["o"], "o"), head_rel_err(s, ref["state"], "state"),
+                  head_rel_err(r, ref["resp"], "resp"))
+    ep = _prior_err(p, ref["prior"])
+    print("o %.3e state %.3e resp %.3e prior %.3e (tol %.0e)" % (eo, es, er, ep, tol))
+    assert eo <= tol and es <= tol and er <= tol and ep <= tol
+
+
 def test_temporal_saturated_gates_equal_plain():
     """Gates at 1 (logit 40, sigmoid 1 in fp32) give the plain recurrence."""
     import torch
