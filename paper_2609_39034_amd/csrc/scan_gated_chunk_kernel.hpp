@@ -218,82 +218,48 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         bool deep_n = false, deep_n1 = false;   // chunk n, n+1 past the factorised Gram products
 
         // E^-1 (in a deep chunk the gates) and E_C of chunk m for component tj from
-        // its decay logits (lane: key index lane, or 2 lane and 2 lane + 1 when
-        // Dk = 128); returns whether the chunk is deep.
+        // its decay logits (lane: key indices 2 lane and 2 lane + 1); returns whether the
+        // chunk is deep.
         auto log_gates = [&](int m) {
             if constexpr (!GT) {
                 return false;
             } else if constexpr (HG) {   // formed by the gate waves
                 return sm.deep[m % 3][tj] != 0;
             } else {
+            static_assert(HG || !GT || DK == 128, "tile waves form the gates of J = 3, Dk = 128 alone");
             const int nt = min(kGC, T - m * kGC);
             bool deep = false;
             auto *const EI = ei_of(m);
-            if constexpr (DK == 128) {
-                // two adjacent key indices per lane
-                const int i = 2 * lane;
-                uint32_t x[kGC];
+            // two adjacent key indices per lane
+            const int i = 2 * lane;
+            uint32_t x[kGC];
 #pragma unroll
-                for (int t = 0; t < kGC; ++t)
-                    x[t] = *reinterpret_cast<const uint32_t *>(&sm.g[t][tj * DK + i]);
-                float c0 = 1.0f, c1 = 1.0f;
+            for (int t = 0; t < kGC; ++t)
+                x[t] = *reinterpret_cast<const uint32_t *>(&sm.g[t][tj * DK + i]);
+            float c0 = 1.0f, c1 = 1.0f;
 #pragma unroll
-                for (int t = 0; t < kGC; ++t) {
-                    const float f0 = 1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] << 16));
-                    const float f1 =
-                        1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] & 0xffff0000u));
-                    c0 *= t < nt ? f0 : 1.0f;
-                    c1 *= t < nt ? f1 : 1.0f;
-                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(c0, c1);
-                }
-                *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) = make_float2(rcp_fast(c0), rcp_fast(c1));
-                deep = !(c0 <= kGramEinv) || !(c1 <= kGramEinv);
-                if (__any(deep) == 0) return false;
-                // deep chunk: the gates, in place of E^-1
-                float l0 = 1.0f, l1 = 1.0f;
-#pragma unroll
-                for (int t = 0; t < kGC; ++t) {
-                    const float a0 = t < nt ? sigmoid(__uint_as_float(x[t] << 16)) : 1.0f;
-                    const float a1 = t < nt ? sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 1.0f;
-                    l0 *= a0, l1 *= a1;
-                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(a0, a1);
-                }
-                *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) = make_float2(l0, l1);
-                return true;
-            } else {
-                // one key index per lane (lanes past Dk idle)
-                const int i = lane, ic = DK >= 64 || i < DK ? i : 0;
-                float x[kGC];
-#pragma unroll
-                for (int t = 0; t < kGC; ++t) x[t] = bf(sm.g[t][tj * DK + ic]);
-                // tokens past the end decay nothing: the chunk's last row is the
-                // product over its last token
-                float cum = 1.0f, e[kGC];
-#pragma unroll
-                for (int t = 0; t < kGC; ++t) {
-                    const float f = 1.0f + __builtin_amdgcn_exp2f(-kLog2e * x[t]);
-                    cum *= t < nt ? f : 1.0f;
-                    e[t] = cum;
-                }
-                if (DK >= 64 || i < DK) {
-#pragma unroll
-                    for (int t = 0; t < kGC; ++t) EI[t][i] = e[t];
-                    sm.ec[m % C::NEC][tj][i] = rcp_fast(cum);
-                    deep = !(cum <= kGramEinv);
-                }
-                if (__any(deep) == 0) return false;
-                if (DK >= 64 || i < DK) {
-                    float l = 1.0f;
-#pragma unroll
-                    for (int t = 0; t < kGC; ++t) {
-                        const float at = t < nt ? sigmoid(x[t]) : 1.0f;
-                        l *= at;
-                        EI[t][i] = at;
-                    }
-                    sm.ec[m % C::NEC][tj][i] = l;
-                }
-                return true;
+            for (int t = 0; t < kGC; ++t) {
+                const float f0 = 1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] << 16));
+                const float f1 =
+                    1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] & 0xffff0000u));
+                c0 *= t < nt ? f0 : 1.0f;
+                c1 *= t < nt ? f1 : 1.0f;
+                *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(c0, c1);
             }
+            *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) = make_float2(rcp_fast(c0), rcp_fast(c1));
+            deep = !(c0 <= kGramEinv) || !(c1 <= kGramEinv);
+            if (__any(deep) == 0) return false;
+            // deep chunk: the gates, in place of E^-1
+            float l0 = 1.0f, l1 = 1.0f;
+#pragma unroll
+            for (int t = 0; t < kGC; ++t) {
+                const float a0 = t < nt ? sigmoid(__uint_as_float(x[t] << 16)) : 1.0f;
+                const float a1 = t < nt ? sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 1.0f;
+                l0 *= a0, l1 *= a1;
+                *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(a0, a1);
+            }
+            *reinterpret_cast<float2 *>(&sm.ec[m % C::NEC][tj][i]) = make_float2(l0, l1);
+            return true;
             }
         };
 
@@ -684,8 +650,9 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             token(ITag<4>{}), token(ITag<5>{}), token(ITag<6>{}), token(ITag<7>{});
             token(ITag<8>{}), token(ITag<9>{}), token(ITag<10>{}), token(ITag<11>{});
             token(ITag<12>{}), token(ITag<13>{}), token(ITag<14>{}), token(ITag<15>{});
-            // (an integer test on bits the compiler cannot trace back to a float:
-            // a NaN, whose magnitude bits exceed those of 2^100, must fail it too)
+            // (an integer test on the magnitude bits, which an infinity fails.  fmaxf
+            // drops a NaN; for finite inputs a NaN sum comes only after one that was
+            // infinite or zero, whose z or 1 / z fails the test)
             uint32_t chk_bits = __float_as_uint(chk);
             asm volatile("" : "+v"(chk_bits));
             const bool bad = (chk_bits & 0x7fffffffu) > 0x71800000u;   // 2^100

@@ -61,13 +61,13 @@ template <int DK, int J, int DB>
 struct GCfg {
     static constexpr int IT = DK / 16;       // 16-row key tiles
     static constexpr int N = J * DB;         // columns, col = j * DB + dd
-    static constexpr int JP = J == 3 ? 4 : J;
+    static constexpr int JP = J;             // lanes per output dim
     static constexpr int NWAVE = J + 1 + kGH;
     static constexpr int KP = DK + 4;        // bf16 row pitch of the K, Q tiles
     static constexpr int LP = DK + 4;        // fp32 row pitch of E^-1 (or the gates)
     static constexpr int TP = kGC + 4;       // [column][token] row pitch
     static constexpr int NP = N + 4;         // [token][column] row pitch
-    static_assert(J >= 1 && J <= 4 && J * DK <= 512, "LDS budget of the gated chunk form");
+    static_assert(J == 4 && DK == 128, "the other shapes run scan_gated_chunk_kernel");
     static_assert(DB == 8 || DB == 16, "column block");
     static_assert(DB * JP <= 64, "one sequential wave");
 };
@@ -133,76 +133,41 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
         bool deep_n = false, deep_n1 = false;   // chunk n, n+1 past the factorised Gram products
 
         // E^-1 (in a deep chunk the gates) and E_C of chunk m for component tj from
-        // its decay logits (lane: key index lane, or 2 lane and 2 lane + 1 when
-        // Dk = 128); returns whether the chunk is deep.
+        // its decay logits (lane: key indices 2 lane and 2 lane + 1); returns whether the
+        // chunk is deep.
         auto log_gates = [&](int m) {
             const int nt = min(kGC, T - m * kGC);
             bool deep = false;
-            if constexpr (DK == 128) {
-                // two adjacent key indices per lane
-                const int i = 2 * lane;
-                uint32_t x[kGC];
+            // two adjacent key indices per lane
+            const int i = 2 * lane;
+            uint32_t x[kGC];
 #pragma unroll
-                for (int t = 0; t < kGC; ++t)
-                    x[t] = *reinterpret_cast<const uint32_t *>(&sm.g[t][tj * DK + i]);
-                float c0 = 1.0f, c1 = 1.0f;
+            for (int t = 0; t < kGC; ++t)
+                x[t] = *reinterpret_cast<const uint32_t *>(&sm.g[t][tj * DK + i]);
+            float c0 = 1.0f, c1 = 1.0f;
 #pragma unroll
-                for (int t = 0; t < kGC; ++t) {
-                    const float f0 = 1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] << 16));
-                    const float f1 =
-                        1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] & 0xffff0000u));
-                    c0 *= t < nt ? f0 : 1.0f;
-                    c1 *= t < nt ? f1 : 1.0f;
-                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(c0, c1);
-                }
-                *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) = make_float2(rcp_fast(c0), rcp_fast(c1));
-                deep = !(c0 <= kGramEinv) || !(c1 <= kGramEinv);
-                if (__any(deep) == 0) return false;
-                // deep chunk: the gates, in place of E^-1
-                float l0 = 1.0f, l1 = 1.0f;
-#pragma unroll
-                for (int t = 0; t < kGC; ++t) {
-                    const float a0 = t < nt ? sigmoid(__uint_as_float(x[t] << 16)) : 1.0f;
-                    const float a1 = t < nt ? sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 1.0f;
-                    l0 *= a0, l1 *= a1;
-                    *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(a0, a1);
-                }
-                *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) = make_float2(l0, l1);
-                return true;
-            } else {
-                // one key index per lane (lanes past Dk idle)
-                const int i = lane, ic = DK >= 64 || i < DK ? i : 0;
-                float x[kGC];
-#pragma unroll
-                for (int t = 0; t < kGC; ++t) x[t] = bf(sm.g[t][tj * DK + ic]);
-                // tokens past the end decay nothing: the chunk's last row is the
-                // product over its last token
-                float cum = 1.0f, e[kGC];
-#pragma unroll
-                for (int t = 0; t < kGC; ++t) {
-                    const float f = 1.0f + __builtin_amdgcn_exp2f(-kLog2e * x[t]);
-                    cum *= t < nt ? f : 1.0f;
-                    e[t] = cum;
-                }
-                if (DK >= 64 || i < DK) {
-#pragma unroll
-                    for (int t = 0; t < kGC; ++t) EI[t][i] = e[t];
-                    sm.ec[m & 1][tj][i] = rcp_fast(cum);
-                    deep = !(cum <= kGramEinv);
-                }
-                if (__any(deep) == 0) return false;
-                if (DK >= 64 || i < DK) {
-                    float l = 1.0f;
-#pragma unroll
-                    for (int t = 0; t < kGC; ++t) {
-                        const float at = t < nt ? sigmoid(x[t]) : 1.0f;
-                        l *= at;
-                        EI[t][i] = at;
-                    }
-                    sm.ec[m & 1][tj][i] = l;
-                }
-                return true;
+            for (int t = 0; t < kGC; ++t) {
+                const float f0 = 1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] << 16));
+                const float f1 =
+                    1.0f + __builtin_amdgcn_exp2f(-kLog2e * __uint_as_float(x[t] & 0xffff0000u));
+                c0 *= t < nt ? f0 : 1.0f;
+                c1 *= t < nt ? f1 : 1.0f;
+                *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(c0, c1);
             }
+            *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) = make_float2(rcp_fast(c0), rcp_fast(c1));
+            deep = !(c0 <= kGramEinv) || !(c1 <= kGramEinv);
+            if (__any(deep) == 0) return false;
+            // deep chunk: the gates, in place of E^-1
+            float l0 = 1.0f, l1 = 1.0f;
+#pragma unroll
+            for (int t = 0; t < kGC; ++t) {
+                const float a0 = t < nt ? sigmoid(__uint_as_float(x[t] << 16)) : 1.0f;
+                const float a1 = t < nt ? sigmoid(__uint_as_float(x[t] & 0xffff0000u)) : 1.0f;
+                l0 *= a0, l1 *= a1;
+                *reinterpret_cast<float2 *>(&EI[t][i]) = make_float2(a0, a1);
+            }
+            *reinterpret_cast<float2 *>(&sm.ec[m & 1][tj][i]) = make_float2(l0, l1);
+            return true;
         };
 
         // four bf16 of row tl of X, key indices 16 it + 4 lg .. + 3, times f
@@ -227,17 +192,11 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
                     Qe[it] = row4(sm.q[s3], it, er);
                     return row4(sm.k[s3], it, x);
                 };
-                if constexpr (IT == 1) {
-                    const S4<2> kinv = operands(0);
-                    g = mm<2>(Kp[0], kinv, g);      // D[t = 4 lg + r][s = tl] = G_ts
-                    qg = mm<2>(kinv, Qe[0], qg);    // D[s = 4 lg + r][t = tl] = QG_ts
-                } else {
 #pragma unroll
-                    for (int it = 0; it < IT; it += 2) {
-                        const S4<2> k0 = operands(it), k1 = operands(it + 1);
-                        g = mmx2<2>(Kp[it], Kp[it + 1], k0, k1, g);
-                        qg = mmx2<2>(k0, k1, Qe[it], Qe[it + 1], qg);
-                    }
+                for (int it = 0; it < IT; it += 2) {
+                    const S4<2> k0 = operands(it), k1 = operands(it + 1);
+                    g = mmx2<2>(Kp[it], Kp[it + 1], k0, k1, g);
+                    qg = mmx2<2>(k0, k1, Qe[it], Qe[it + 1], qg);
                 }
                 // lane (tl, lg) holds QG[t = tl][s = 4 lg + r]: the A operand of the retrieval
 #pragma unroll
@@ -260,17 +219,11 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
         // for the sequential wave, in its units, and Q S (Y0q)
         auto predict = [&]() {
             floatx4 pacc = floatx4{0.f, 0.f, 0.f, 0.f}, y0 = floatx4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (IT == 1) {
-                const S4<2> ws = split4<2>(W[0]);
-                pacc = mm<2>(Kp[0], ws, pacc);   // D[t][col]
-                y0 = mm<2>(Qe[0], ws, y0);
-            } else {
 #pragma unroll
-                for (int it = 0; it < IT; it += 2) {
-                    const S4<2> w0 = split4<2>(W[it]), w1 = split4<2>(W[it + 1]);
-                    pacc = mmx2<2>(Kp[it], Kp[it + 1], w0, w1, pacc);
-                    y0 = mmx2<2>(Qe[it], Qe[it + 1], w0, w1, y0);
-                }
+            for (int it = 0; it < IT; it += 2) {
+                const S4<2> w0 = split4<2>(W[it]), w1 = split4<2>(W[it + 1]);
+                pacc = mmx2<2>(Kp[it], Kp[it + 1], w0, w1, pacc);
+                y0 = mmx2<2>(Qe[it], Qe[it + 1], w0, w1, y0);
             }
             if (tvalid)
                 *reinterpret_cast<float4 *>(&sm.p[tcol][4 * lg]) =
@@ -482,8 +435,9 @@ __global__ __launch_bounds__(512) void scan_gated_chunk_wide_kernel(LayerArgs a)
 #pragma unroll
                 for (int u = t + 2; u < kGC; ++u) gprev[u] = grow[u], grow[u] = gnext[u];
             }
-            // (an integer test on bits the compiler cannot trace back to a float:
-            // a NaN, whose magnitude bits exceed those of 2^100, must fail it too)
+            // (an integer test on the magnitude bits, which an infinity fails.  fmaxf
+            // drops a NaN; for finite inputs a NaN sum comes only after one that was
+            // infinite or zero, whose z or 1 / z fails the test)
             uint32_t chk_bits = __float_as_uint(chk);
             asm volatile("" : "+v"(chk_bits));
             const bool bad = (chk_bits & 0x7fffffffu) > 0x71800000u;   // 2^100

@@ -1235,9 +1235,9 @@ void scan_pipe_kernel(LayerArgs a, NewtonArgs na) {
                         // chk is the largest z and 1/z seen (one max3 per token):
                         // above 2^100 iff some z left [2^-100, 2^100]
                         float chk = 0.f, cprev = 0.f, cb[4], d = D[0][0];
-                        // (an integer test on bits the compiler cannot trace back to a
-                        // float: the file is compiled without NaN semantics, and a NaN,
-                        // whose magnitude bits exceed those of 2^100, must fail it too)
+                        // (an integer test on the magnitude bits, which an infinity fails.
+                        // fmaxf drops a NaN; for finite inputs a NaN sum comes only after
+                        // one that was infinite or zero, whose z or 1 / z fails the test)
                         auto bad = [&]() {
                             uint32_t chk_bits = __float_as_uint(chk);
                             asm volatile("" : "+v"(chk_bits));
