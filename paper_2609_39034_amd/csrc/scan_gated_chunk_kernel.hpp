@@ -150,8 +150,8 @@ struct GSmem {
     // in scaled units)} [column][token] (beta = 0 past the end) and s v [dim][token]; temporal: {beta,
     // g^k pi^k} and 1 - g^k [dim][token]
     alignas(16) float2 sq[2][C::N][kGC + 2];
-    // (row DB: zeros, the idle lanes')
-    alignas(16) float vs[2][DB + 1][kGC + 4];
+    // (J = 3: row DB zeros, the padding lanes')
+    alignas(16) float vs[2][DB + (J == 3)][kGC + 4];
     alignas(16) float gs[TP ? 2 : 1][TP ? DB : 1][kGC + 4];
     alignas(16) In lk[TP ? 2 : 1][TP ? kGC : 1][TP ? C::N : 8];   // temporal: key-prior logits
     float gq[TP ? 3 : 1][TP ? kGC : 1][TP ? DB : 1];        // temporal: g^q, chunk m in m % 3
@@ -160,8 +160,9 @@ struct GSmem {
     // subdiagonal, [j][s] = that of token s + 1
     alignas(16) float gt[2][J][kGC][kGC];
     alignas(16) float gsub[2][J][kGC];
-    // chunk-start predictions, times s [column][token] (row N: zeros, the idle lanes')
-    alignas(16) float p[C::N + 1][C::CP];
+    // chunk-start predictions, times s [column][token] (J = 3: row N zeros, the padding
+    // lanes')
+    alignas(16) float p[C::N + (J == 3)][C::CP];
     // coefficients [column][token], chunk m in m & 1 (row N: the idle lanes')
     alignas(16) float c[2][C::N + 1][C::CP];
     float pq[2][kGC][C::NP];                 // pi^q [token][column]
@@ -486,10 +487,12 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         const int sdd = lane / 16 * C::SD + lane % C::SD, sj = lane % 16 / C::SD;
         const bool sact = sdd < DB && sj < J;
         const int scol = sact ? sj * DB + sdd : 0, gj = sact ? sj : 0;
-        // Idle lanes, the padding component of J = 3 among them, which is summed with
-        // the others of its dim, read rows of zeros: another column's v or predictions
-        // would carry what is not finite there to this dim.
         const int scst = sact ? scol : N;
+        // The padding component of J = 3 is summed with the others of its dim: its lanes
+        // read rows of zeros, since another column's v or predictions would carry what is
+        // not finite there to this dim.  (Lanes of no dim read column 0.)
+        constexpr bool PAD = J == 3;
+        const int spre = sact ? scol : PAD ? N : 0;
         const bool wres = a.resp && sact;
         auto lane_sum = [](float x) {
             if constexpr (JP >= 4) x += dpp_mov<0x124>(x);   // row_ror 4
@@ -503,8 +506,9 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
         };
         float sbeta[kGC], slk[kGC], sgs[TP ? kGC : 1];
         floatx4 sv[kGC / 4];
-        const int vdd = sact ? sdd : DB;
-        if (lane < kGC) sm.p[N][lane] = sm.vs[0][DB][lane] = sm.vs[1][DB][lane] = 0.0f;   // (read by this wave alone)
+        const int vdd = sact ? sdd : PAD ? DB : 0;
+        if constexpr (PAD)   // (read by this wave alone)
+            if (lane < kGC) sm.p[N][lane] = sm.vs[0][DB][lane] = sm.vs[1][DB][lane] = 0.0f;
         // r_{t-1} of this lane's column (temporal), and that of the last token
         float rprev = 0.0f, rlast = 0.0f;
         if constexpr (TP) {
@@ -562,7 +566,7 @@ __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void sc
             auto start = [&]() {
 #pragma unroll
                 for (int i = 0; i < kGC / 4; ++i) {
-                    const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[scst][4 * i]);
+                    const float4 p4 = *reinterpret_cast<const float4 *>(&sm.p[spre][4 * i]);
                     const floatx4 p = floatx4{p4.x, p4.y, p4.z, p4.w};
                     D[i] = C::SCALED ? sv[i] - p : -p;
                 }
