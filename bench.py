@@ -298,20 +298,18 @@ def bench_temporal(sw, torch, workloads, dev, cfg, seed, steps, warmup, o, s_out
     kern = sum(a.elapsed_time(b) for a, b in ev) / steps / 1e3
     bf16 = cfg["dtype"] == "bf16"
     eb = 2 if bf16 else 4
-    chunk = algo == "chunk" or (algo == "auto" and bf16)
+    chunk, kname, ksrc = scan_kernel("temporal", cfg, algo)
     nbytes = temporal_alg_bytes(B, H, T, Dk, Dv, J, eb, eb, dev["state"] is not None, True)
     return {
         "workload": "Temporal SwiLA (App. B.3), B=%d H=%d T=%d Dk=Dv=%d J=%d, N(0,1) gate "
                     "logits, uniform initial priors, final prior state kept" % (B, H, T, Dk, J),
         "tokens_per_s": B * T / wall, "ms_per_step": wall * 1e3,
-        "algo": "chunk_exact" if chunk else "recurrent",
+        "algo": form_name(cfg, chunk),
         "roofline": {"bound": "hbm", "achieved": nbytes / kern / 1e9, "peak": PEAK_HBM / 1e9,
                      "unit": "GB/s", "frac": nbytes / kern / PEAK_HBM,
-                     "traffic": (measured_traffic("scan_pipe_temporal.hip",
-                                                  workload_key("temporal", B, H, T, Dk, Dv, J))
-                                 if chunk else None),
-                     "kernel": ("scan_pipe_kernel (temporal mode)" if chunk
-                                else "scan_direct_kernel (temporal)"),
+                     "traffic": measured_traffic(ksrc, workload_key("temporal", B, H, T, Dk,
+                                                                    Dv, J)),
+                     "kernel": kname + (" (temporal mode)" if chunk else " (temporal)"),
                      "kernel_ms": kern * 1e3, "alg_bytes_per_launch": nbytes},
     }
 
@@ -382,10 +380,39 @@ def bench_backward(sw, torch, dev, cfg, steps, warmup):
     }
 
 
-def gated_chunk_form(cfg):
-    """Whether SWILA_ALGO_AUTO runs the gated form in chunks on the matrix cores
-    (bf16 inputs, J <= 4, J * Dk <= 512, no temporal priors)."""
-    return cfg["dtype"] == "bf16" and cfg["J"] <= 4 and cfg["J"] * cfg["Dk"] <= 512
+def scan_kernel(kind, cfg, algo):
+    """(chunk form?, kernel, source) of the scan that ``algo`` runs on workload
+    ``cfg``; kind is "forward", "temporal" or "gated".  bf16 inputs take the exact
+    chunk scan; bf16 gated ones (J <= 4, J * Dk <= 512) the gated chunk scan, whose
+    J * Dk > 384 is a kernel of its own.  fp32 inputs take the chunk form in three
+    bf16 parts (J <= 4, J * Dk <= 256), by AUTO alone and where it is the faster one
+    by length and grid: c1 (T=64 J=2, one column block), the one workload with fp32
+    inputs, is such a call."""
+    Dk, J = cfg["Dk"], cfg["J"]
+    direct = (False, "scan_direct_kernel", "scan_direct_dk%d.hip" % Dk)
+    if algo == "recurrent":
+        return direct
+    if cfg["dtype"] != "bf16":
+        if algo == "chunk" or J > 4 or J * Dk > 256:
+            return direct
+        return True, "scan_gated_chunk_kernel", ("scan_chunk_f32_gated.hip" if kind == "gated"
+                                                 else "scan_chunk_f32.hip")
+    if kind == "gated":
+        if J > 4 or J * Dk > 512:
+            return direct
+        if J * Dk > 384:
+            return True, "scan_gated_chunk_wide_kernel", "scan_gated_chunk_wide.hip"
+        return True, "scan_gated_chunk_kernel", "scan_gated_chunk.hip"
+    if J > 8:
+        return direct
+    return True, "scan_pipe_kernel", ("scan_pipe_temporal.hip" if kind == "temporal"
+                                      else "scan_pipe.hip")
+
+
+def form_name(cfg, chunk):
+    """How a line names its form: the exact chunk form of bf16 inputs, that of fp32
+    inputs (AUTO alone takes it), or the token-by-token scan."""
+    return ("chunk_exact" if cfg["dtype"] == "bf16" else "chunk_f32") if chunk else "recurrent"
 
 
 def bench_gated(sw, torch, workloads, dev, cfg, seed, steps, warmup, o, s_out, tdt):
@@ -420,7 +447,7 @@ def bench_gated(sw, torch, workloads, dev, cfg, seed, steps, warmup, o, s_out, t
               + eb * J * Dk * B * H * T)
     # the method's FMAs plus the decay: one multiply per state element and token
     nflop = forward_alg_flops(B, H, T, Dk, Dv, J) + J * Dk * Dv * B * H * T
-    chunk = gated_chunk_form(cfg)
+    chunk, kname, ksrc = scan_kernel("gated", cfg, "auto")
     key = workload_key("gated", B, H, T, Dk, Dv, J)
     alu = {"bound": "alu", "achieved": nflop / kern / 1e12, "peak": PEAK_VALU_F32 / 1e12,
            "unit": "TFLOP/s", "frac": nflop / kern / PEAK_VALU_F32,
@@ -431,12 +458,10 @@ def bench_gated(sw, torch, workloads, dev, cfg, seed, steps, warmup, o, s_out, t
     if chunk:
         # the Dk-long products run on the matrix cores: the HBM roofline, as for
         # the plain chunk scan, with the fp32-ALU figure beside it
-        roof = dict(hbm, kernel="scan_gated_chunk_kernel",
-                    traffic=measured_traffic("scan_gated_chunk.hip", key))
-        other = dict(alu, kernel="scan_gated_chunk_kernel")
+        roof = dict(hbm, kernel=kname, traffic=measured_traffic(ksrc, key))
+        other = dict(alu, kernel=kname)
     else:
-        roof = dict(alu, kernel="scan_direct_kernel (gated)",
-                    traffic=measured_traffic("scan_direct_dk%d.hip" % Dk, key))
+        roof = dict(alu, kernel=kname + " (gated)", traffic=measured_traffic(ksrc, key))
         other = None
     return {
         "workload": "Gated SwiLA (App. B.4, pre-decay, one gate per key dim), B=%d H=%d T=%d "
@@ -444,7 +469,7 @@ def bench_gated(sw, torch, workloads, dev, cfg, seed, steps, warmup, o, s_out, t
                     % (B, H, T, Dk, J, "chunks of 16 tokens on the matrix cores" if chunk
                        else "token-by-token scan"),
         "tokens_per_s": B * T / wall, "ms_per_step": wall * 1e3,
-        "algo": "chunk_exact" if chunk else "recurrent",
+        "algo": form_name(cfg, chunk),
         "roofline": roof, "roofline_other": other,
     }
 
@@ -526,9 +551,7 @@ def bench_forward(sw, torch, workloads, cfg_id, steps, warmup, algo, inp=None):
     o = torch.empty((B, T, H, Dv), device="cuda", dtype=tdt)
     s_out = torch.empty((B, H, J, Dk, Dv), device="cuda", dtype=torch.float32)
     wall, kern = time_forward(sw, torch, dev, steps, warmup, o, s_out, algo)
-    chunk = algo == "chunk" or (algo == "auto" and bf16 and J <= 8)
-    kname, ksrc = (("scan_pipe_kernel", "scan_pipe.hip") if chunk
-                   else ("scan_direct_kernel", "scan_direct_dk%d.hip" % Dk))
+    chunk, kname, ksrc = scan_kernel("forward", cfg, algo)
     eb = 2 if bf16 else 4
     nbytes = forward_alg_bytes(B, H, T, Dk, Dv, J, eb, eb, dev["state"] is not None, True)
     nflop = forward_alg_flops(B, H, T, Dk, Dv, J)
@@ -547,13 +570,17 @@ def bench_forward(sw, torch, workloads, cfg_id, steps, warmup, algo, inp=None):
         "workload": "SwiLA forward, %s: B=%d H=%d T=%d Dk=Dv=%d J=%d, %s inputs, fp32 state, "
                     "zero initial state, seeded" % (cfg["name"], B, H, T, Dk, J, cfg["dtype"]),
         "B": B, "H": H, "T": T, "Dk": Dk, "Dv": Dv, "J": J,
-        "algo": "chunk_exact" if chunk else "recurrent",
+        "algo": form_name(cfg, chunk),
         "tokens_per_s": B * T / wall, "ms_per_step": wall * 1e3, "us_per_step": wall * 1e6,
         "roofline": roof, "roofline_other": other,
     }
     return res, dev, o, s_out, wall
 
 
+# what the forms compute in, by inputs and form
+ARITH_CHUNK_F32 = ("fp32 state, fp32 scalar recurrence and E-step; the Dk-long products on "
+                   "bf16 matrix cores with each fp32 operand split into three bf16 parts, "
+                   "fp32 accumulation; fp32 inputs and output")
 ARITH = ("fp32 state, fp32 scalar recurrence and E-step; the Dk-long products on bf16 "
          "matrix cores with each fp32 operand split into a bf16 high part and a bf16 "
          "residual (hi*hi + hi*lo + lo*hi, about 2^-16 relative per product), fp32 "
@@ -620,13 +647,14 @@ def main():
     inp = workloads.config_inputs(args.config)
     head, dev, o, s_out, wall = bench_forward(sw, torch, workloads, args.config, args.steps,
                                               args.warmup, args.algo, inp=inp)
-    chunk = head["algo"] == "chunk_exact"
+    chunk = head["algo"] != "recurrent"
     out = {
         "metric": METRIC, "value": B * T / wall, "unit": "tokens/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": wall * 1e3,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32+bf16x3" if chunk else "f32",
-        "arith": ARITH if chunk else "fp32 throughout on the vector ALUs",
+        "arith": ((ARITH if bf16 else ARITH_CHUNK_F32) if chunk
+                  else "fp32 throughout on the vector ALUs"),
         "io_dtype": "bf16" if bf16 else "f32", "data": "synthetic",
         "config": {"workload": head["workload"], "B": B, "H": H, "T": T, "Dk": Dk, "Dv": Dv,
                    "J": J, "algo": head["algo"]},
