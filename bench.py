@@ -43,19 +43,21 @@ PEAK_MFMA_F32 = 157.3e12   # FLOP/s, MI355X dense fp32 matrix
 # source, the workload it ran and the digest of the source at measurement.
 MEASURED_TRAFFIC = {
     ("scan_pipe.hip", "forward B=8 H=16 T=4096 Dk=Dv=128 J=4",
-     "69a737312b74bd8f3dedd808d43ac8367b2dbf9b21ccca372790ce9b8cebd952"): 2185222850,
-    ("scan_pipe.hip", "forward B=4 H=8 T=2048 Dk=Dv=64 J=4",
-     "69a737312b74bd8f3dedd808d43ac8367b2dbf9b21ccca372790ce9b8cebd952"): 136707495,
-    ("scan_pipe.hip", "forward B=2 H=8 T=16384 Dk=Dv=128 J=8",
-     "69a737312b74bd8f3dedd808d43ac8367b2dbf9b21ccca372790ce9b8cebd952"): 2797221636,
+     "6ca5a4fb421b572d3ced465089f9923152245519db2f06a898ae27e7c23774d6"): 2181524149,
     ("scan_pipe_temporal.hip", "temporal B=8 H=16 T=4096 Dk=Dv=128 J=4",
-     "41604fc349b073c09ba91bf77ad77b546ac62f0e66f6d17093fb967cc91b2027"): 2450471795,
-    ("scan_gated_chunk.hip", "gated B=8 H=16 T=4096 Dk=Dv=128 J=4",
-     "3521c3b9f68a659ea24c176dfcb5d3ac4e3060cceb8b7219c8ae445ec250cf44"): 2720938128,
-    ("decode.hip", "decode B=256 H=16 Dk=Dv=128 J=4",
-     "a4c73fb2a97e003cf707dbe2b81c1b57afaee61077b4cfc79a6a3f9889745265"): 2166168222,
+     "aa74d0f761626f956efb8044abe0997f2392d3b1521637cb2d94c0ba349425bd"): 2451653386,
+    ("scan_gated_chunk_wide.hip", "gated B=8 H=16 T=4096 Dk=Dv=128 J=4",
+     "5ab546876c6c322f0889b155d2ad352650112bbdeed1da262456dde2d7a1c158"): 2719555500,
+    ("scan_chunk_f32.hip", "forward B=1 H=1 T=64 Dk=Dv=16 J=2",
+     "46b18006eb6e098e1432452270829cf9256a8403fbe3b03c3a804bdfb3baf5cd"): 163452,
+    ("scan_pipe.hip", "forward B=4 H=8 T=2048 Dk=Dv=64 J=4",
+     "6ca5a4fb421b572d3ced465089f9923152245519db2f06a898ae27e7c23774d6"): 137426063,
     ("scan_gated_chunk.hip", "gated B=4 H=8 T=2048 Dk=Dv=64 J=4",
-     "3521c3b9f68a659ea24c176dfcb5d3ac4e3060cceb8b7219c8ae445ec250cf44"): 170459080,
+     "07f395d6808c1caeee53642975c0abe3b785d4eeaf5e2ec3d164b41662ae8d07"): 170603298,
+    ("scan_pipe.hip", "forward B=2 H=8 T=16384 Dk=Dv=128 J=8",
+     "6ca5a4fb421b572d3ced465089f9923152245519db2f06a898ae27e7c23774d6"): 1889867708,
+    ("decode.hip", "decode B=256 H=16 Dk=Dv=128 J=4",
+     "76b7bed1728617dcb49a9fc2f70756e90508a3726a53e73d0a7709af4080b7e8"): 2165462070,
 }
 
 
