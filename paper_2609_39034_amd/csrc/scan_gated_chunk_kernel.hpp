@@ -53,8 +53,8 @@
 // Bound: the tile waves' operands (phase A 3,500 cycles a chunk at Dk = 64, the
 // sequential wave 2,900 on the SIMD it shares with one of them), then phase B's
 // 1,050.  One launch at B=4 H=8 T=2048 D=64 J=4, before (deferred updates as
-// multiply-adds, gates by the tile waves) and now: 0.364 -> 0.281 ms; with the
-// temporal priors, before on the token-by-token scan: 1.261 -> 0.414 ms.
+// multiply-adds, gates by the tile waves) and now: 0.364 -> 0.287 ms; with the
+// temporal priors, before on the token-by-token scan: 1.261 -> 0.404 ms.
 //
 // The same kernel evaluates fp32 inputs (F32), with or without gates (GT) and
 // temporal priors: K and Q are then fp32 operands like the state, every operand
@@ -174,6 +174,9 @@ struct GSmem {
 // role meets the same block barriers in the same order: four in the prologue,
 // two per chunk (e(n): C_n and chunk n + 2 published; i(n+1): P_{n+1}
 // published), one in the epilogue.
+// (Nine and ten waves a block cap a lane at 168 registers.  Four instantiations spill,
+// 8 to 12 bytes a lane: gates and priors, bf16 <32, 4, 8>, <64, 4, 16> and
+// <128, 1, 16>, fp32 <32, 4, 16>.)
 template <int DK, int J, int DB, bool TP, bool GT, bool F32>
 __global__ __launch_bounds__((64 * GCfg<DK, J, DB, TP, GT, F32>::NWAVE)) void scan_gated_chunk_kernel(LayerArgs a) {
     using C = GCfg<DK, J, DB, TP, GT, F32>;
